@@ -105,7 +105,9 @@ int64_t tbn_packed_bytes(int64_t k, int64_t n);
  * Pass the same op and geometry to the corresponding call.  TBN_OP_FWD: fp32 partial sums
  * of a split reduction, or, for inputs with fewer than 8 channels and at least 2^20
  * elements, a zero-bordered bf16 copy of the input with the channels padded to a power of
- * two (the forward call writes it first); the size covers either input dtype. */
+ * two (the forward call writes it first); the size covers either input dtype.  Channel counts
+ * that are no multiple of 8 (C, and K in the backward passes) add a copy of the tensor with the
+ * channels padded to one. */
 tbn_status tbn_workspace_size(tbn_op op, const tbn_conv_desc* desc, size_t* bytes);
 
 /*
@@ -165,9 +167,11 @@ tbn_status tbn_conv2d_fwd(const tbn_conv_desc* desc, const void* x, tbn_dtype xt
  * one per device, held until the process ends, its address looked up on the first call on
  * each device.  The call allocates nothing.  A layer whose tbn_workspace_size(TBN_OP_FWD)
  * exceeds TBN_NOALLOC_SCRATCH_BYTES gets TBN_ERR_WORKSPACE (nothing queued); every batch-1
- * layer of the workloads fits.  All calls on one device share its array: calls whose work
- * overlaps in time on that device (other streams, other host threads) race on it and must
- * be serialised by the caller; calls on one stream are ordered and safe.
+ * layer of the workloads fits.  A layer whose workspace only holds a channel-padded copy
+ * (C > 8, C % 8 != 0) runs without it, on the general kernel, and uses no scratch.  All calls
+ * on one device share the array: calls whose work overlaps in time on that device (other
+ * streams, other host threads) race on it and must be serialised by the caller; calls on one
+ * stream are ordered and safe.
  */
 #define TBN_NOALLOC_SCRATCH_BYTES (8u << 20)
 tbn_status tbn_conv2d_fwd_noalloc(const tbn_conv_desc* desc, const void* x, tbn_dtype xt, const uint32_t* codes,

@@ -90,31 +90,47 @@ int wgrad_splits(const Geometry& g) {
     return (int)splits;
 }
 
-// bwd_weight of an input with C < 8 channels (and K % 8 == 0): run on the LDS-DMA kernel
-// over the input copied into 8 channels.  Workspace: the 8-channel input, then the split
-// partials of the 8-channel gradient.
-bool wgrad_pad8(const Geometry& g, Geometry* g8) {
-    if (g.C >= 8 || g.K % 8 != 0) return false;
-    *g8 = g;
-    g8->C = 8;
-    if (g8->R * g8->S * 8 > kI32Max / 2) return false;
-    return tbn::wgrad_dma_eligible(wgrad_args(*g8));
+// bwd_weight with C or K no multiple of 8: x copied into Cp and dy into Kp channels (zeros
+// beyond the real ones) so that the LDS-DMA kernel applies; the real rows and channels of its
+// Kp x Cp-channel partials are summed.  `gp` is the padded geometry.  Workspace: the copy of x
+// (if C is padded), the copy of dy (if K is), the partials.
+struct WgradPad {
+    Geometry gp;
+    int splits;
+    int64_t dy_off, partial_off, total;
+    bool required;  // the workspace this layer has always needed; otherwise without it (or with
+                    // less) the register-staged kernel runs
+};
+
+int64_t channel_copy_bytes(int64_t pixels, int64_t channels) { return round_up(pixels * channels * 2, 256); }
+
+bool wgrad_pad(const Geometry& g, WgradPad* p) {
+    if (g.C % 8 == 0 && g.K % 8 == 0) return false;
+    p->gp = g;
+    p->gp.C = round_up(g.C, 8);
+    p->gp.K = round_up(g.K, 8);
+    if (product_over(g.R, g.S, p->gp.C, kI32Max / 2) || product_over(g.R, g.S, p->gp.K, kI32Max / 2)) return false;
+    if (!tbn::wgrad_dma_eligible(wgrad_args(p->gp))) return false;
+    p->splits = wgrad_splits(p->gp);
+    p->dy_off = g.C % 8 ? channel_copy_bytes(g.N * g.H * g.W, p->gp.C) : 0;
+    p->partial_off = p->dy_off + (g.K % 8 ? channel_copy_bytes(g.N * g.P * g.Q, p->gp.K) : 0);
+    p->total = p->partial_off + (int64_t)p->splits * (p->gp.K * g.R * g.S * p->gp.C) * 4;
+    p->required = (g.C < 8 && g.K % 8 == 0) || g.C % 8 == 0;
+    return true;
 }
 
-int64_t pad8_x_bytes(const Geometry& g) { return round_up(g.N * g.H * g.W * 16, 256); }
-
 // A gradient with K % 8 != 0 channels (a 10-way classifier): dy copied into Kp = K rounded
-// up to 8 channels (zeros beyond K) so that both backward passes run on the LDS-DMA
-// kernels.  `gk` is the geometry with Kp filters.
+// up to 8 channels (zeros beyond K) so that backward-data runs on the LDS-DMA kernel.  `gk` is
+// the geometry with Kp filters.
 bool grad_padk(const Geometry& g, Geometry* gk) {
-    if (g.K % 8 == 0 || g.C % 8 != 0) return false;
+    if (g.K % 8 == 0) return false;
     *gk = g;
     gk->K = round_up(g.K, 8);
     if (gk->R * gk->S * gk->K > kI32Max / 2) return false;
     return true;
 }
 
-int64_t padk_dy_bytes(const Geometry& gk) { return round_up(gk.N * gk.P * gk.Q * gk.K * 2, 256); }
+int64_t padk_dy_bytes(const Geometry& gk) { return channel_copy_bytes(gk.N * gk.P * gk.Q, gk.K); }
 
 struct BwdDataWs {
     int64_t codes_bytes, apair_off, apair_bytes, partial_off, partial_bytes, total;
@@ -160,9 +176,23 @@ tbn::ConvGemmArgs bwd_data_args(const Geometry& g, tbn_dtype dxt) {
     return a;
 }
 
+// Forward workspace without which a call is refused, over both input types.
+size_t fwd_required_bytes(const Geometry& g) {
+    const size_t b16 = tbn::conv_gemm_partial_bytes(fwd_args(g, TBN_BF16, TBN_BF16));
+    const size_t b32 = tbn::conv_gemm_partial_bytes(fwd_args(g, TBN_F32, TBN_BF16));
+    return b16 > b32 ? b16 : b32;
+}
+
 }  // namespace
 
 namespace tbn {
+tbn_status fwd_required_workspace(const tbn_conv_desc* desc, size_t* bytes) {
+    Geometry g;
+    tbn_status st = check_desc(desc, &g);
+    if (st == TBN_OK) *bytes = fwd_required_bytes(g);
+    return st;
+}
+
 tbn_status set_error(tbn_status s, const std::string& what) {
     g_last_error = what;
     return s;
@@ -219,9 +249,12 @@ tbn_status tbn_workspace_size(tbn_op op, const tbn_conv_desc* desc, size_t* byte
     switch (op) {
         case TBN_OP_FWD: {
             // the same geometry may take another path for fp32 input: size for both
-            const size_t b16 = tbn::conv_gemm_partial_bytes(fwd_args(g, TBN_BF16, TBN_BF16));
-            const size_t b32 = tbn::conv_gemm_partial_bytes(fwd_args(g, TBN_F32, TBN_BF16));
-            *bytes = b16 > b32 ? b16 : b32;
+            size_t most = fwd_required_bytes(g);
+            for (const tbn_dtype xt : {TBN_BF16, TBN_F32}) {
+                tbn::ConvPadPlan pp;
+                if (tbn::conv_pad_plan(fwd_args(g, xt, TBN_BF16), &pp) && (size_t)pp.total > most) most = (size_t)pp.total;
+            }
+            *bytes = most;
             return TBN_OK;
         }
         case TBN_OP_BWD_DATA: {
@@ -231,17 +264,14 @@ tbn_status tbn_workspace_size(tbn_op op, const tbn_conv_desc* desc, size_t* byte
             return TBN_OK;
         }
         case TBN_OP_BWD_WEIGHT: {
-            Geometry g8;
-            if (wgrad_pad8(g, &g8)) {
-                *bytes = (size_t)pad8_x_bytes(g) + (size_t)wgrad_splits(g8) * (size_t)(g.K * g.R * g.S * 8) * 4;
-                return TBN_OK;
-            }
-            if (grad_padk(g, &g8) && tbn::wgrad_dma_eligible(wgrad_args(g8))) {
-                *bytes = (size_t)padk_dy_bytes(g8) + (size_t)wgrad_splits(g8) * (size_t)(g8.K * g.R * g.S * g.C) * 4;
-                return TBN_OK;
-            }
+            WgradPad wp;
+            const bool padded = wgrad_pad(g, &wp);
+            *bytes = padded ? (size_t)wp.total : 0;
+            if (padded && wp.required) return TBN_OK;
+            // without the padded copies (or where a caller gives less than they need)
             const int splits = wgrad_splits(g);
-            *bytes = splits > 1 ? (size_t)splits * (size_t)(g.K * g.R * g.S * g.C) * 4 : 0;
+            const size_t plain = splits > 1 ? (size_t)splits * (size_t)(g.K * g.R * g.S * g.C) * 4 : 0;
+            if (plain > *bytes) *bytes = plain;
             return TBN_OK;
         }
     }
@@ -310,7 +340,9 @@ tbn_status tbn_conv2d_fwd(const tbn_conv_desc* desc, const void* x, tbn_dtype xt
         a.relu = ep->relu ? 1 : 0;
     }
     a.y = y;
-    hipError_t e = tbn::launch_conv_gemm(a, stream);
+    tbn::ConvPadPlan pp;
+    const bool padded = ws && aligned16(ws) && tbn::conv_pad_plan(a, &pp) && ws_bytes >= (size_t)pp.total;
+    hipError_t e = padded ? tbn::launch_conv_padded(a, pp, ws, stream) : tbn::launch_conv_gemm(a, stream);
     return e == hipSuccess ? TBN_OK : hip_fail(e, "tbn_conv2d_fwd");
 }
 
@@ -373,11 +405,18 @@ tbn_status tbn_conv2d_bwd_data(const tbn_conv_desc* desc, const void* dy, const 
         return fail(TBN_ERR_ALIGN, "dy, codes and dx must be 16-byte aligned");
     // K % 8 != 0: the GEMM runs over dy copied into Kp channels (workspace, after the rest)
     Geometry gk;
-    const bool padk = grad_padk(g, &gk);
+    bool padk = grad_padk(g, &gk);
+    BwdDataWs w = bwd_data_ws(padk ? gk : g);
+    int64_t dy_off = round_up(w.total, 256);  // the Kp-channel copy of dy (padk only)
+    int64_t total = padk ? dy_off + padk_dy_bytes(gk) : w.total;
+    if (padk && g.C % 8 != 0 && ws_bytes < (size_t)total) {
+        // C % 8 != 0 as well: with only the workspace of the unpadded layer the general kernel
+        // runs it as it is
+        padk = false;
+        w = bwd_data_ws(g);
+        total = w.total;
+    }
     const Geometry& gg = padk ? gk : g;
-    const BwdDataWs w = bwd_data_ws(gg);
-    const int64_t dy_off = round_up(w.total, 256);  // the Kp-channel copy of dy (padk only)
-    const int64_t total = padk ? dy_off + padk_dy_bytes(gk) : w.total;
     if (!ws || ws_bytes < (size_t)total) return fail(TBN_ERR_WORKSPACE, "workspace too small");
     if (!aligned16(ws)) return fail(TBN_ERR_ALIGN, "workspace must be 16-byte aligned");
     uint32_t* codes_t = reinterpret_cast<uint32_t*>(ws);
@@ -411,56 +450,39 @@ tbn_status tbn_conv2d_bwd_weight(const tbn_conv_desc* desc, const void* x, const
     if (st != TBN_OK) return st;
     if (!x || !dy || !dw) return fail(TBN_ERR_NULL, "x, dy and dw are required");
     if (!aligned16(x) || !aligned16(dy) || !aligned16(dw)) return fail(TBN_ERR_ALIGN, "misaligned pointer");
-    Geometry g8;
-    if (wgrad_pad8(g, &g8)) {
-        // few input channels: 8-channel copy of x, 8-channel gradient, channels < C kept
-        const int splits = wgrad_splits(g8);
-        const int64_t xb = pad8_x_bytes(g);
-        const size_t need = (size_t)xb + (size_t)splits * (size_t)(g.K * g.R * g.S * 8) * 4;
-        if (!ws || ws_bytes < need) return fail(TBN_ERR_WORKSPACE, "workspace too small");
+    WgradPad wp;
+    if (wgrad_pad(g, &wp) && (wp.required || (ws && aligned16(ws) && ws_bytes >= (size_t)wp.total))) {
+        if (!ws || ws_bytes < (size_t)wp.total) return fail(TBN_ERR_WORKSPACE, "workspace too small");
         if (!aligned16(ws)) return fail(TBN_ERR_ALIGN, "workspace must be 16-byte aligned");
-        uint16_t* x8 = reinterpret_cast<uint16_t*>(ws);
-        float* part = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + xb);
-        hipError_t e = tbn::launch_pad_channels(reinterpret_cast<const uint16_t*>(x), g.N * g.H * g.W, (int32_t)g.C, 8,
-                                                x8, stream);
-        if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
-        tbn::WgradArgs a = wgrad_args(g8);
-        a.x = x8;
-        a.dy = reinterpret_cast<const uint16_t*>(dy);
-        a.out = part;
-        const int64_t chunks = (g.N * g.P * g.Q + 63) / 64;
-        a.splits = splits;
-        a.chunks_per_split = (int32_t)((chunks + splits - 1) / splits);
-        a.accumulate = 0;
-        e = tbn::launch_wgrad(a, stream);
-        if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight");
-        e = tbn::launch_split_reduce_compact(part, splits, g.K * g.R * g.S, (int32_t)g.C, dw, accumulate, stream);
-        return e == hipSuccess ? TBN_OK : hip_fail(e, "tbn_conv2d_bwd_weight (reduce)");
-    }
-    if (grad_padk(g, &g8) && tbn::wgrad_dma_eligible(wgrad_args(g8))) {
-        // K % 8 != 0: dy copied into Kp channels; rows k < K of the Kp-row partials summed
-        const int splits = wgrad_splits(g8);
-        const int64_t dyb = padk_dy_bytes(g8);
-        const int64_t J = g.R * g.S * g.C;
-        const size_t need = (size_t)dyb + (size_t)splits * (size_t)(g8.K * J) * 4;
-        if (!ws || ws_bytes < need) return fail(TBN_ERR_WORKSPACE, "workspace too small");
-        if (!aligned16(ws)) return fail(TBN_ERR_ALIGN, "workspace must be 16-byte aligned");
-        uint16_t* dyp = reinterpret_cast<uint16_t*>(ws);
-        float* part = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + dyb);
-        hipError_t e = tbn::launch_pad_channels(reinterpret_cast<const uint16_t*>(dy), g.N * g.P * g.Q, (int32_t)g.K,
-                                                (int32_t)g8.K, dyp, stream);
-        if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
-        tbn::WgradArgs a = wgrad_args(g8);
+        const Geometry& gp = wp.gp;
+        uint8_t* const base = reinterpret_cast<uint8_t*>(ws);
+        float* const part = reinterpret_cast<float*>(base + wp.partial_off);
+        tbn::WgradArgs a = wgrad_args(gp);
         a.x = reinterpret_cast<const uint16_t*>(x);
-        a.dy = dyp;
+        a.dy = reinterpret_cast<const uint16_t*>(dy);
+        if (gp.C != g.C) {
+            uint16_t* const xp = reinterpret_cast<uint16_t*>(base);
+            hipError_t e = tbn::launch_pad_channels(a.x, g.N * g.H * g.W, (int32_t)g.C, (int32_t)gp.C, xp, stream);
+            if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
+            a.x = xp;
+        }
+        if (gp.K != g.K) {
+            uint16_t* const dyp = reinterpret_cast<uint16_t*>(base + wp.dy_off);
+            hipError_t e = tbn::launch_pad_channels(a.dy, g.N * g.P * g.Q, (int32_t)g.K, (int32_t)gp.K, dyp, stream);
+            if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
+            a.dy = dyp;
+        }
         a.out = part;
         const int64_t chunks = (g.N * g.P * g.Q + 63) / 64;
-        a.splits = splits;
-        a.chunks_per_split = (int32_t)((chunks + splits - 1) / splits);
+        a.splits = wp.splits;
+        a.chunks_per_split = (int32_t)((chunks + wp.splits - 1) / wp.splits);
         a.accumulate = 0;
-        e = tbn::launch_wgrad(a, stream);
+        hipError_t e = tbn::launch_wgrad(a, stream);
         if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight");
-        e = tbn::launch_split_reduce(part, splits, g.K * J, g8.K * J, dw, accumulate, stream);
+        const int64_t rows = g.K * g.R * g.S, stride = gp.K * g.R * g.S * gp.C;
+        e = gp.C != g.C ? tbn::launch_split_reduce_compact(part, wp.splits, rows, stride, (int32_t)g.C, (int32_t)gp.C, dw,
+                                                           accumulate, stream)
+                        : tbn::launch_split_reduce(part, wp.splits, rows * g.C, stride, dw, accumulate, stream);
         return e == hipSuccess ? TBN_OK : hip_fail(e, "tbn_conv2d_bwd_weight (reduce)");
     }
     const int splits = wgrad_splits(g);

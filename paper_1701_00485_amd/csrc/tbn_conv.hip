@@ -408,6 +408,49 @@ size_t conv_gemm_partial_bytes(const ConvGemmArgs& a) {
     }
 }
 
+static ConvGemmArgs padded_args(const ConvGemmArgs& a, int32_t Cp) {
+    ConvGemmArgs b = a;
+    b.C = Cp;
+    b.x_f32 = 0;
+    return b;
+}
+
+// C % 8 != 0 beyond the few-channel kernels: two launches (the copies, then the LDS-DMA
+// kernel) instead of the general kernel's one, and faster at every size tried (graph-replayed,
+// general -> padded): 1 x 1 x 20 -> 32 filters 14.2 -> 5.4 us, 14 x 14 x 100 -> 100 3 x 3 at batch 1
+// 205 -> 12.9 us, 50 x 27 x 27 x 36 -> 100 3 x 3 130 -> 21.3 us, 64 rows of 3001 -> 500 611 -> 12.6 us
+// (the general kernel gathers 2-byte elements with a division and a bounds test each).
+bool conv_pad_plan(const ConvGemmArgs& a, ConvPadPlan* p) {
+    const int cfg = conv_tile_override();
+    FcStreamPlan fp;
+    ThinGeom tg;
+    if (a.apair || cfg >= 0 || a.C % 8 == 0 || choose_path(a, cfg, &fp, &tg) != PATH_GENERIC) return false;
+    const int64_t Cp = ((int64_t)a.C + 7) / 8 * 8;
+    if ((int64_t)a.R * a.S * Cp >= (1 << 30)) return false;
+    const ConvGemmArgs b = padded_args(a, (int32_t)Cp);
+    if (!conv_dma_eligible(b)) return false;
+    p->Cp = (int32_t)Cp;
+    const int64_t xb = (int64_t)a.N * a.H * a.W * Cp * 2;
+    p->codes_off = (xb + 255) / 256 * 256;
+    const int64_t cb = (int64_t)((a.Kf + 63) / 64) * (((int64_t)a.R * a.S * Cp + 63) / 64) * 1024;
+    p->partial_off = p->codes_off + cb;
+    p->total = p->partial_off + (int64_t)plan_conv_dma(b, cfg).partial_bytes;
+    return true;
+}
+
+hipError_t launch_conv_padded(const ConvGemmArgs& a, const ConvPadPlan& p, void* ws, hipStream_t stream) {
+    uint8_t* const base = reinterpret_cast<uint8_t*>(ws);
+    uint32_t* const codes_p = reinterpret_cast<uint32_t*>(base + p.codes_off);
+    hipError_t e = launch_pad_fwd(a.x, a.x_f32, (int64_t)a.N * a.H * a.W, a.C, p.Cp, base, a.codes, a.Kf, a.R * a.S,
+                                  codes_p, stream);
+    if (e != hipSuccess) return e;
+    ConvGemmArgs b = padded_args(a, p.Cp);
+    b.x = base;
+    b.codes = codes_p;
+    b.partial = reinterpret_cast<float*>(base + p.partial_off);
+    return launch_conv_gemm(b, stream);
+}
+
 hipError_t launch_conv_gemm(const ConvGemmArgs& args, hipStream_t stream) {
     ConvGemmArgs a = args;
     a.div_q = make_fastdiv((uint32_t)a.Q);

@@ -18,6 +18,10 @@ int knob(int which);
 // Record the detail of an error for tbn_last_error() on this thread; returns s.
 tbn_status set_error(tbn_status s, const std::string& what);
 
+// Forward workspace without which tbn_conv2d_fwd refuses a layer (tbn_workspace_size may ask
+// for more, with which the layer runs faster).
+tbn_status fwd_required_workspace(const tbn_conv_desc* desc, size_t* bytes);
+
 // Unsigned division by a runtime constant d >= 1 for numerators below 2^31
 // (round-up multiplier: q = (mulhi(n, mul) + n) >> shift).
 struct FastDiv {
@@ -114,6 +118,14 @@ int conv_tile_override();
 int conv_splits_override();
 // Bytes of split-K partials the forward / backward-data GEMM of these arguments needs.
 size_t conv_gemm_partial_bytes(const ConvGemmArgs& a);
+// A forward layer that only the general kernel takes as it is because C % 8 != 0 (bf16 or fp32
+// input): copied and re-packed into workspace (total bytes) it runs on the LDS-DMA kernel.
+struct ConvPadPlan {
+    int32_t Cp;
+    int64_t codes_off, partial_off, total;
+};
+bool conv_pad_plan(const ConvGemmArgs& a, ConvPadPlan* p);
+hipError_t launch_conv_padded(const ConvGemmArgs& a, const ConvPadPlan& p, void* ws, hipStream_t stream);
 
 // Forward pass for inputs with few channels (C < 8 bf16, or fp32 with C <= 8): input patch
 // and decoded filters staged in LDS with the channels padded to a power of two.
@@ -180,13 +192,33 @@ struct WgradDmaPlan {
 WgradDmaPlan wgrad_dma_plan(int K, int J);
 hipError_t launch_wgrad_dma(const WgradArgs& a, hipStream_t stream);
 
-// Channel counts the LDS-DMA kernels cannot take (C < 8 inputs, K % 8 != 0 gradients): the
-// tensor copied into Cp channels (a multiple of 8, zeros beyond C); for the filter gradient
-// of a C < 8 input, the 8-channel gradient's split partials summed into the C-channel dw.
+// Channel counts the LDS-DMA kernels cannot take (tbn_pad.hip): a tensor copied into Cp
+// channels (a multiple of 8, zeros beyond C), as bf16, and the codes of a forward layer
+// re-packed to match.
+struct PadArgs {
+    const void* x;  // [pixels][C] bf16 or fp32
+    uint16_t* xp;   // [pixels][Cp] bf16
+    int64_t pixels, blocks;
+    int32_t C, Cp;
+    int32_t small;  // fewer than 2^31 groups: 32-bit magic-number division
+    FastDiv div_groups;
+};
+struct RepackFwdArgs {
+    const uint32_t* codes;  // TBN2 codes of filters of taps * C elements
+    uint32_t* out;          // ... of taps * Cp elements
+    int64_t words;          // of out
+    int32_t C, Cp, taps, nb;
+    uint32_t nbp;
+    FastDiv div_cp, div_nbp;
+};
 hipError_t launch_pad_channels(const uint16_t* x, int64_t pixels, int32_t C, int32_t Cp, uint16_t* xp,
                                hipStream_t stream);
-hipError_t launch_split_reduce_compact(const float* partials, int32_t splits, int64_t rows, int32_t C, float* dw,
-                                       int32_t accumulate, hipStream_t stream);
+hipError_t launch_pad_fwd(const void* x, int x_f32, int64_t pixels, int32_t C, int32_t Cp, void* xp,
+                          const uint32_t* codes, int32_t K, int32_t taps, uint32_t* codes_p, hipStream_t stream);
+// partials [splits][stride] of a Cp-channel filter gradient, channels c < C of the first
+// `rows` rows kept: dw[row][c] (+)= sum_z
+hipError_t launch_split_reduce_compact(const float* partials, int32_t splits, int64_t rows, int64_t stride, int32_t C,
+                                       int32_t Cp, float* dw, int32_t accumulate, hipStream_t stream);
 // partials [splits][stride]: dw[i] (+)= sum_z partials[z][i] for i < count
 hipError_t launch_split_reduce(const float* partials, int32_t splits, int64_t count, int64_t stride, float* dw,
                                int32_t accumulate, hipStream_t stream);

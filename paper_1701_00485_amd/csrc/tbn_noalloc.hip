@@ -49,8 +49,10 @@ tbn_status scratch_ptr(void** out) {
 extern "C" tbn_status tbn_conv2d_fwd_noalloc(const tbn_conv_desc* desc, const void* x, tbn_dtype xt,
                                              const uint32_t* codes, const float* alpha, const tbn_epilogue* ep,
                                              void* y, tbn_dtype yt, hipStream_t stream) {
+    // only what a layer cannot run without: a layer that would merely run faster with a
+    // workspace keeps off the shared array, so that its calls may overlap in time
     size_t need = 0;
-    tbn_status st = tbn_workspace_size(TBN_OP_FWD, desc, &need);
+    tbn_status st = tbn::fwd_required_workspace(desc, &need);
     if (st != TBN_OK) return st;
     if (need > (size_t)TBN_NOALLOC_SCRATCH_BYTES)
         return tbn::set_error(TBN_ERR_WORKSPACE, "the layer needs " + std::to_string(need) +

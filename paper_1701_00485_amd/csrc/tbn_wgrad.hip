@@ -286,39 +286,36 @@ __global__ __launch_bounds__(256) void split_reduce_groups_kernel(const float* _
     }
 }
 
-// An NHWC tensor with C channels copied into Cp channels (Cp a multiple of 8, zeros in
-// channels C..Cp-1), so that the LDS-DMA kernels (8-channel granularity) apply.  One thread
-// per pixel and 8-channel group.
-__global__ __launch_bounds__(256) void pad_channels_kernel(const uint16_t* __restrict__ x, int64_t pixels, int32_t C,
-                                                           int32_t Cp, uint16_t* __restrict__ xp) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int groups = Cp / 8;
-    if (i >= pixels * groups) return;
-    const int64_t pix = i / groups;
-    const int c0 = (int)(i - pix * groups) * 8;
-    uint32_t v[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = c0 + c < C ? x[pix * C + c0 + c] : 0u;
-    *reinterpret_cast<u32x4*>(xp + pix * Cp + c0) =
-        u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
-}
-
-// Sum of the split partials of an 8-channel filter gradient [splits][rows][8], keeping
-// channels c < C: dw[row][c] (+)= sum_z part[z][row][c], G threads per output adding every
-// G-th split, combined in group order (fixed).
+// Sum of the split partials of a channel-padded filter gradient [splits][stride] with rows of
+// Cp channels, keeping channels c < C: dw[row][c] (+)= sum_z part[z][row][c], G threads per
+// output adding every G-th split (eight loads in flight where one thread adds them all),
+// combined in group order (fixed).
 template <int G>
 __global__ __launch_bounds__(256) void split_reduce_compact_kernel(const float* __restrict__ part, int32_t splits,
-                                                                   int64_t rows, int32_t C, float* __restrict__ dw,
+                                                                   int64_t rows, int64_t stride, int32_t C, int32_t Cp,
+                                                                   FastDiv div_c, float* __restrict__ dw,
                                                                    int32_t accumulate) {
     constexpr int OPB = 256 / G;
     __shared__ float sh[256];
     const int o = threadIdx.x % OPB, g = threadIdx.x / OPB;
     const int64_t i = (int64_t)blockIdx.x * OPB + o;  // output (row, c)
     const int64_t count = rows * C;
-    const int64_t src = (i / C) * 8 + i % C;
+    const int64_t row = count < 0x7FFFFFFF ? (int64_t)fdiv((uint32_t)i, div_c) : i / C;
+    const int64_t src = row * Cp + (i - row * C);
     float s = 0.0f;
-    if (i < count)
-        for (int z = g; z < splits; z += G) s += part[(int64_t)z * rows * 8 + src];
+    if (i < count) {
+        int z = g;
+        if constexpr (G == 1) {
+            for (; z + 8 <= splits; z += 8) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(z + u) * stride + src];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += v[u];
+            }
+        }
+        for (; z < splits; z += G) s += part[(int64_t)z * stride + src];
+    }
     sh[threadIdx.x] = s;
     __syncthreads();
     if (g == 0 && i < count) {
@@ -330,23 +327,16 @@ __global__ __launch_bounds__(256) void split_reduce_compact_kernel(const float* 
 
 }  // namespace
 
-hipError_t launch_pad_channels(const uint16_t* x, int64_t pixels, int32_t C, int32_t Cp, uint16_t* xp,
-                               hipStream_t stream) {
-    const int64_t n = pixels * (Cp / 8);
-    hipLaunchKernelGGL(pad_channels_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, x, pixels, C, Cp,
-                       xp);
-    return hipGetLastError();
-}
-
-hipError_t launch_split_reduce_compact(const float* partials, int32_t splits, int64_t rows, int32_t C, float* dw,
-                                       int32_t accumulate, hipStream_t stream) {
+hipError_t launch_split_reduce_compact(const float* partials, int32_t splits, int64_t rows, int64_t stride, int32_t C,
+                                       int32_t Cp, float* dw, int32_t accumulate, hipStream_t stream) {
     const int64_t count = rows * C;
+    const FastDiv div_c = make_fastdiv((uint32_t)C);
     if (count < 65536 && splits >= 32)
         hipLaunchKernelGGL(split_reduce_compact_kernel<16>, dim3((unsigned)((count + 15) / 16)), dim3(256), 0, stream,
-                           partials, splits, rows, C, dw, accumulate);
+                           partials, splits, rows, stride, C, Cp, div_c, dw, accumulate);
     else
         hipLaunchKernelGGL(split_reduce_compact_kernel<1>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream,
-                           partials, splits, rows, C, dw, accumulate);
+                           partials, splits, rows, stride, C, Cp, div_c, dw, accumulate);
     return hipGetLastError();
 }
 
