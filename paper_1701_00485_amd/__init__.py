@@ -2,8 +2,12 @@
 
 A thin ctypes layer over the C ABI in ``include/tbn.h``.  It only marshals arguments:
 torch supplies device memory and the current stream, and every step of the computation
-runs in the library's HIP kernels.  If ``libtbn.so`` is missing or does not load, every
-call raises; there is no fallback.
+runs in the library's HIP kernels.  If ``libtbn.so`` or ``_tbn_torch.so`` is missing or does
+not load, every call raises; there is no fallback.
+
+Ordinary calls (plain dense GPU tensors of the expected types and sizes) are marshalled in
+native code (``native/tbn_torch.cpp``), which declines everything else; what it declines takes
+the ctypes code below, whose checks raise the errors.
 
 Calls (same names as the C ABI, without the ``tbn_`` prefix):
   quantize(w)                      Sec. 2 Eq. (3)-(5)   -> packed codes, alpha, counts
@@ -17,17 +21,20 @@ Calls (same names as the C ABI, without the ``tbn_`` prefix):
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtbn.so")
+BINDING_PATH = os.path.join(_HERE, "_tbn_torch.so")
 
 TBN_BF16, TBN_F32 = 0, 1
 OP_FWD, OP_BWD_DATA, OP_BWD_WEIGHT = 0, 1, 2
 
 _lib = None
+_native = None
 
 
 class TbnError(RuntimeError):
@@ -112,6 +119,20 @@ def load():
         fn.restype = res
     _lib = lib
     return lib
+
+
+def _load_native():
+    """The native marshalling module (built in-tree by build.py); raises if it is missing."""
+    global _native
+    load()
+    if not os.path.exists(BINDING_PATH):
+        raise RuntimeError("_tbn_torch.so not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
+    spec = importlib.util.spec_from_file_location("_tbn_torch", BINDING_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.bind_types(ConvDesc, TbnError)
+    _native = mod
+    return mod
 
 
 def exported_symbols():
@@ -230,6 +251,9 @@ def _numel(t, expect, name):
 
 def quantize(w: torch.Tensor, codes=None, alpha=None, counts=None, want_counts=True):
     """w: [K][n] fp32 (or [K][R][S][C]).  Returns (codes int32 words, alpha fp32, counts)."""
+    out = (_native or _load_native()).quantize(w, codes, alpha, counts, want_counts)
+    if out is not NotImplemented:
+        return out
     K = w.shape[0]
     n = w.numel() // K
     pw = _dev(w, "w", (torch.float32,))
@@ -304,6 +328,9 @@ def conv2d_fwd(desc: ConvDesc, x, codes, alpha, y=None, out_dtype=torch.bfloat16
                residual=None, relu=False, ws=None):
     """y = act(alpha_k * scale_k * (x conv W~) + bias_k + residual), NHWC.  `ws`: workspace
     of workspace_size(OP_FWD, desc) bytes (allocated here when None and needed)."""
+    out = (_native or _load_native()).conv2d_fwd(desc, x, codes, alpha, y, out_dtype, scale, bias, residual, relu, ws)
+    if out is not NotImplemented:
+        return out
     P, Q = desc.out_dims()
     _numel(x, desc.n * desc.h * desc.w * desc.c, "x")
     _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
@@ -335,6 +362,9 @@ def conv2d_fwd(desc: ConvDesc, x, codes, alpha, y=None, out_dtype=torch.bfloat16
 def quantize_act_i8(x: torch.Tensor, inv_scale: float, q=None):
     """int8 activation codes q = clamp(round-half-even(x * inv_scale), -127, 127) (NaN -> 0),
     elementwise over a bf16 or fp32 tensor; returns q (int8, x's shape)."""
+    out = (_native or _load_native()).quantize_act_i8(x, inv_scale, q)
+    if out is not NotImplemented:
+        return out
     if q is None:
         q = torch.empty(x.shape, dtype=torch.int8, device=x.device)
     _numel(q, x.numel(), "q")
@@ -346,6 +376,9 @@ def quantize_act_i8(x: torch.Tensor, inv_scale: float, q=None):
 def conv2d_fwd_i8(desc: ConvDesc, xq, codes, alpha, x_scale: float, y=None, out_dtype=torch.bfloat16, relu=False):
     """Forward pass on int8 activation codes (int8 matrix cores):
     y = act(float(xq conv W~) * float(alpha_k * x_scale)), NHWC."""
+    out = (_native or _load_native()).conv2d_fwd_i8(desc, xq, codes, alpha, x_scale, y, out_dtype, relu)
+    if out is not NotImplemented:
+        return out
     P, Q = desc.out_dims()
     _numel(xq, desc.n * desc.h * desc.w * desc.c, "xq")
     _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
@@ -362,6 +395,9 @@ def conv2d_fwd_i8(desc: ConvDesc, xq, codes, alpha, x_scale: float, y=None, out_
 def quantize_act_fp8(x: torch.Tensor, inv_scale: float, q=None):
     """E4M3 activation codes f = E4M3(x * inv_scale) (nearest, ties to even, saturating at
     +-448, NaN -> 0), elementwise over a bf16 or fp32 tensor; returns the codes (uint8)."""
+    out = (_native or _load_native()).quantize_act_fp8(x, inv_scale, q)
+    if out is not NotImplemented:
+        return out
     if q is None:
         q = torch.empty(x.shape, dtype=torch.uint8, device=x.device)
     _numel(q, x.numel(), "q")
@@ -384,6 +420,9 @@ def conv2d_fwd_fp8(desc: ConvDesc, xq, codes_fp4, alpha, x_scale: float, y=None,
                    relu=False):
     """Forward pass on E4M3 activation codes (scaled fp8 x fp4 matrix cores):
     y = act((f conv W~) * float(alpha_k * x_scale)), NHWC; codes_fp4 from repack_codes_fp4."""
+    out = (_native or _load_native()).conv2d_fwd_fp8(desc, xq, codes_fp4, alpha, x_scale, y, out_dtype, relu)
+    if out is not NotImplemented:
+        return out
     P, Q = desc.out_dims()
     _numel(xq, desc.n * desc.h * desc.w * desc.c, "xq")
     _numel(codes_fp4, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
@@ -401,6 +440,9 @@ def conv2d_fwd_dense(desc: ConvDesc, x, w, y=None, out_dtype=torch.bfloat16, sca
                      residual=None, relu=False):
     """Full-precision layer: y = act(scale_k * (x conv bf16(w)) + bias_k + residual), NHWC;
     w fp32 [K][R][S][C]."""
+    out = (_native or _load_native()).conv2d_fwd_dense(desc, x, w, y, out_dtype, scale, bias, residual, relu)
+    if out is not NotImplemented:
+        return out
     P, Q = desc.out_dims()
     _numel(x, desc.n * desc.h * desc.w * desc.c, "x")
     _numel(w, desc.k * desc.r * desc.s * desc.c, "w")
@@ -424,6 +466,9 @@ def conv2d_fwd_dense(desc: ConvDesc, x, w, y=None, out_dtype=torch.bfloat16, sca
 
 
 def conv2d_bwd_data(desc: ConvDesc, dy, codes, alpha, dx=None, out_dtype=torch.bfloat16, ws=None):
+    out = (_native or _load_native()).conv2d_bwd_data(desc, dy, codes, alpha, dx, out_dtype, ws)
+    if out is not NotImplemented:
+        return out
     P, Q = desc.out_dims()
     _numel(dy, desc.n * P * Q * desc.k, "dy")
     _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
@@ -441,6 +486,9 @@ def conv2d_bwd_data(desc: ConvDesc, dy, codes, alpha, dx=None, out_dtype=torch.b
 
 
 def conv2d_bwd_weight(desc: ConvDesc, x, dy, dw=None, accumulate=False, ws=None):
+    out = (_native or _load_native()).conv2d_bwd_weight(desc, x, dy, dw, accumulate, ws)
+    if out is not NotImplemented:
+        return out
     P, Q = desc.out_dims()
     _numel(x, desc.n * desc.h * desc.w * desc.c, "x")
     _numel(dy, desc.n * P * Q * desc.k, "dy")
@@ -456,6 +504,9 @@ def conv2d_bwd_weight(desc: ConvDesc, x, dy, dw=None, accumulate=False, ws=None)
 
 
 def sgd_step(w, v, g, lr, momentum=0.9, weight_decay=1e-4):
+    out = (_native or _load_native()).sgd_step(w, v, g, lr, momentum, weight_decay)
+    if out is not NotImplemented:
+        return out
     n = w.numel()
     _numel(v, n, "v")
     _numel(g, n, "g")
@@ -468,6 +519,10 @@ def sgd_step_quantize(w, v, g, lr, momentum=0.9, weight_decay=1e-4, codes=None, 
                       want_counts=True):
     """SGD update of w [K][n] (in place, with momentum v) fused with the quantisation of
     the updated filters.  Returns (codes, alpha, counts) as quantize() does."""
+    out = (_native or _load_native()).sgd_step_quantize(w, v, g, lr, momentum, weight_decay, codes, alpha, counts,
+                                                        want_counts)
+    if out is not NotImplemented:
+        return out
     K = w.shape[0]
     n = w.numel() // K
     _numel(v, K * n, "v")
@@ -501,6 +556,9 @@ class PoolDesc(ctypes.Structure):
 
 def maxpool2d_fwd(x, k, stride, pad, want_argmax=False):
     """x NHWC bf16 -> (y, argmax int32 or None)."""
+    out = (_native or _load_native()).maxpool2d_fwd(x, k, stride, pad, want_argmax)
+    if out is not NotImplemented:
+        return out
     n, h, w, c = x.shape
     d = PoolDesc(n, h, w, c, k, stride, pad)
     P, Q = d.out_dims()
@@ -513,6 +571,9 @@ def maxpool2d_fwd(x, k, stride, pad, want_argmax=False):
 
 def maxpool2d_bwd(dy, argmax, x_shape, k, stride, pad, out_dtype=torch.bfloat16):
     n, h, w, c = x_shape
+    out = (_native or _load_native()).maxpool2d_bwd(dy, argmax, n, h, w, c, k, stride, pad, out_dtype)
+    if out is not NotImplemented:
+        return out
     d = PoolDesc(n, h, w, c, k, stride, pad)
     dx = torch.empty(tuple(x_shape), dtype=out_dtype, device=dy.device)
     _call("tbn_maxpool2d_bwd", ctypes.byref(d), _dev(dy, "dy", (torch.bfloat16,)),
@@ -521,6 +582,9 @@ def maxpool2d_bwd(dy, argmax, x_shape, k, stride, pad, out_dtype=torch.bfloat16)
 
 
 def avgpool_global(x, out_dtype=torch.bfloat16):
+    out = (_native or _load_native()).avgpool_global(x, out_dtype)
+    if out is not NotImplemented:
+        return out
     n, h, w, c = x.shape
     y = torch.empty((n, c), dtype=out_dtype, device=x.device)
     _call("tbn_avgpool_global", n, h, w, c, _dev(x, "x", (torch.bfloat16,)), _dev(y, "y"),
@@ -542,6 +606,9 @@ def _bn_ws(rows, c, ws, device):
 
 
 def batchnorm_train_fwd(x, gamma, beta, eps=1e-5, relu=False, ws=None):
+    out = (_native or _load_native()).batchnorm_train_fwd(x, gamma, beta, eps, relu, ws)
+    if out is not NotImplemented:
+        return out
     c = x.shape[-1]
     rows = x.numel() // c
     y = torch.empty_like(x)
@@ -558,6 +625,9 @@ def batchnorm_train_fwd(x, gamma, beta, eps=1e-5, relu=False, ws=None):
 def batchnorm_train_bwd(x, y, dy, mean, inv_std, gamma, relu=False, ws=None, dgamma=None, dbeta=None):
     """Returns (dx, dgamma, dbeta); `dgamma` / `dbeta` may be caller-provided fp32 [C] outputs
     (for example views into one flat gradient buffer)."""
+    out = (_native or _load_native()).batchnorm_train_bwd(x, y, dy, mean, inv_std, gamma, relu, ws, dgamma, dbeta)
+    if out is not NotImplemented:
+        return out
     c = x.shape[-1]
     rows = x.numel() // c
     dx = torch.empty_like(x)
@@ -576,6 +646,9 @@ def batchnorm_train_bwd(x, y, dy, mean, inv_std, gamma, relu=False, ws=None, dga
 
 
 def relu_bwd(y, dy):
+    out = (_native or _load_native()).relu_bwd(y, dy)
+    if out is not NotImplemented:
+        return out
     dx = torch.empty_like(dy)
     _call("tbn_relu_bwd", _dev(y, "y", (torch.bfloat16,)), _dev(dy, "dy", (torch.bfloat16,)), dy.numel(),
           _dev(dx, "dx"), _stream())
@@ -584,6 +657,9 @@ def relu_bwd(y, dy):
 
 def softmax_xent(logits, labels):
     """logits fp32 [n][classes], labels int32 [n] -> (loss fp32 [1], dlogits bf16)."""
+    out = (_native or _load_native()).softmax_xent(logits, labels)
+    if out is not NotImplemented:
+        return out
     n, k = logits.shape
     loss = torch.empty(1, dtype=torch.float32, device=logits.device)
     per = torch.empty(n, dtype=torch.float32, device=logits.device)
