@@ -28,9 +28,9 @@ typedef enum tbn_knob {
     TBN_KNOB_CONV_TILE = 0,
     /* forward / backward-data reduction split (>= 1) */
     TBN_KNOB_CONV_SPLITS = 1,
-    /* weight-gradient stage layout: 0 segment-major, 1 pixel-major */
+    /* weight-gradient kernel: 0 narrow tiles, 1 tiles of 256 x 256 */
     TBN_KNOB_WGRAD_CFG = 2,
-    /* pixel-major weight gradient: pixels per stage (32, 48 or 64) */
+    /* 256 x 256 weight gradient: pixels per stage (32, 48 or 64) */
     TBN_KNOB_WGRAD_PIX = 3,
     /* weight gradient: L2 prefetch this many stages ahead (0 = off) */
     TBN_KNOB_WGRAD_PF = 4,

@@ -182,14 +182,14 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t stream);
 // LDS-DMA + transposing-read variant (C % 8 == 0, K % 8 == 0, tensors < 2 GiB),
 // 256 x 256 output tiles of 512 threads; launch_wgrad uses it when eligible.
 bool wgrad_dma_eligible(const WgradArgs& a);
-// Stage layout of the LDS-DMA weight-gradient kernel (1 = pixel-major rows for K >= 128,
-// 0 = segment-major; the stage-layout knob forces one for tests), its output tiles and how many
-// blocks are resident at once.
+// Kernel of the LDS-DMA weight gradient (1 = 256 x 256 tiles, 0 = narrow tiles; the cfg knob
+// forces one for tests), its tile, output tiles and how many blocks are resident at once.
 struct WgradDmaPlan {
     int cfg, tiles, resident_blocks;
-    int pix;  // pixel-major kernel: pixels per stage (32, 48 or 64)
+    int tk, tj;  // filters x columns of a block tile
+    int pix;     // 256 x 256 kernel: pixels per stage (32, 48 or 64)
 };
-WgradDmaPlan wgrad_dma_plan(int K, int J);
+WgradDmaPlan wgrad_dma_plan(const WgradArgs& a);
 hipError_t launch_wgrad_dma(const WgradArgs& a, hipStream_t stream);
 
 // Channel counts the LDS-DMA kernels cannot take (tbn_pad.hip): a tensor copied into Cp

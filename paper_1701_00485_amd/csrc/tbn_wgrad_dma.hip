@@ -9,21 +9,15 @@
 // operands with the gfx950 transposing LDS read (ds_read_b64_tr_b16: a 16-lane group
 // turns a 16 x 4 block of 16-bit values into 4 consecutive rows per lane), so the main
 // loop spends no vector ALU work on data movement:
-//   * a block of 8 waves owns a 256 (k) x 256 (j) output tile; each wave 128 x 64 made of
-//     32x32 v_mfma_f32_32x32x16_bf16 tiles with fp32 accumulators;
+//   * a block of 8 waves owns an output tile (256 (k) x 256 (j), each wave 128 x 64, for wide
+//     layers) made of 32x32 v_mfma_f32_32x32x16_bf16 tiles with fp32 accumulators;
 //   * stages of pixels in a ring of LDS buffers: the DMAs of later stages overlap the
-//     MFMAs of the current one, and the operands of each 16-pixel step are read two steps
-//     earlier (the pixel-major kernel; one step in the segment-major one);
+//     MFMAs of the current one, and the operands of each 16-pixel step are read one or two
+//     steps earlier;
 //   * the pixel range is split over the grid (split-K): each split writes fp32 partials
 //     that a second kernel adds in a fixed order (deterministic result).
-// Two stage layouts:
-//   * pixel-major (wide layers): each pixel's 256 dy channels / 256 x columns form one
-//     512-byte row of the stage, two pixels per 1088-byte slot, so that one 64-lane DMA
-//     instruction copies two pixels' contiguous bytes and the requests cover whole cache
-//     lines; 48-pixel stages, three deep (an L2 prefetch of a later stage is an option);
-//   * segment-major (K < 128): 64-pixel stages, two deep; for every 8-channel segment the
-//     64 pixels' 16-byte pieces are contiguous (one DMA instruction, lane = pixel),
-//     segments 1088 bytes apart; with few valid dy channels this issues fewer copies.
+// Two kernels: 256 x 256 tiles for wide layers, narrow tiles where K or J would leave most of
+// such a tile empty.
 #include <cstdlib>
 #include <type_traits>
 
@@ -35,24 +29,10 @@ namespace tbn {
 
 namespace {
 
-constexpr int SEGS = 32;             // 8-channel segments of the dy tile (256 channels)
-constexpr int TILE_K = 256;
-
-// Stage geometry: PIXS pixels per stage; each 8-channel segment holds the PIXS pixels'
-// 16-byte pieces contiguously, segments padded by 64 bytes (bank spread of the
-// transposing reads of neighbouring segments).  A stage holds the 32 dy segments, then
-// the 8 WN x segments (TILE_J = 64 WN columns).
-template <int PIXS, int WN>
-struct WgStage {
-    static constexpr int SEG_PITCH = PIXS * 16 + 64;
-    static constexpr int OP_BYTES = SEGS * SEG_PITCH;          // dy tile
-    static constexpr int BYTES = (SEGS + 8 * WN) * SEG_PITCH;  // dy tile then x tile
-};
-
 struct WgradDmaArgs {
     WgradArgs a;
     FastDiv div_q, div_pq;
-    int32_t pf_dist;  // pixel-major kernel: stages between a copy and the L2 prefetch issued with it
+    int32_t pf_dist;  // wide kernel: stages between a copy and the L2 prefetch issued with it
 };
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
@@ -68,15 +48,6 @@ __device__ __forceinline__ uint32_t lane_select(uint64_t mask, uint32_t if_clear
     uint32_t r;
     asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(if_clear), "v"(if_set), "s"(mask));
     return r;
-}
-
-// 8 consecutive pixels of one channel as an MFMA operand (two transposing reads).
-__device__ __forceinline__ bf16x8 operand(uint32_t addr) {
-    const v4i16 lo = read_tr(addr);
-    const v4i16 hi = read_tr(addr + 64);  // pixels + 4
-    typedef short v8i16 __attribute__((ext_vector_type(8)));
-    const v8i16 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
 }
 
 // Instruction order of one 16-pixel step: its 8 MFMAs alternate with the 12 transposing
@@ -99,99 +70,174 @@ __device__ __forceinline__ void interleave_reads() {
     }
 }
 
-// Segment-major variant: 64-pixel stages, two-deep LDS ring, 2 x 4 waves (wave tile
-// 128 x 64, block tile 256 x 256).
-__global__ __launch_bounds__(512, 1) void wgrad_seg_kernel(const WgradDmaArgs ka) {
-    constexpr int PIXS = 64, STAGES = 2, WN = 4;
-    const WgradArgs& a = ka.a;
-    constexpr int TM = 4, TN = 2;  // wave tile 128 x 64
-    constexpr int TILE_J = 64 * WN;
-    constexpr int DYQ = SEGS / (2 * WN);  // dy segments each wave copies
-    using L = WgStage<PIXS, WN>;
-    constexpr int SEG_PITCH = L::SEG_PITCH;
-    constexpr int OP_BYTES = L::OP_BYTES;
+// Narrow variant: block tiles of TK x TJ = 32 TM WM x 32 TN WN (filters x columns) for layers
+// whose K or J leaves most of a 256 x 256 tile empty.  A block is two groups of four waves; each
+// group reduces its own half of the split's pixels with its own LDS ring, and group 1 hands its
+// sums to group 0 through LDS (half as many partial gradients in memory as with two blocks).
+//
+// A stage holds PIX pixels as rows of the dy tile, then rows of the x tile, copied 1 KiB at a
+// time: with RS = 8-channel segments per row an LDS-DMA instruction takes 64 / RS whole rows, so
+// requests cover runs of TK or TJ channels.  Which memory piece a lane fetches is free, where it
+// lands is not, so the bank spread comes from the fetch: slot s of pixel p holds segment s ^ f(p),
+//   f(p) = 4 (p % 4) for RS >= 16, 4 (p / 2 % 2) for RS = 8, 0 for RS = 4,
+// and the 8 pixels x 64 bytes of a transposing read cover every bank exactly twice.
+// Where each pixel's taps start in x comes from a table in LDS (byte offset, top-left
+// coordinates): one wave of the group fills it for a later stage, so that a copy costs a lane one
+// LDS read and about nine vector operations rather than two divisions.
+//
+// One barrier per stage, ahead of its last 16-pixel step: stage it + 1 has landed and every wave
+// holds the operands of stage it's last step, so the copies of stage it + STAGES go into its slot
+// and the next stage's first operands are read under that step's MFMAs.
+struct TapEntry {
+    uint32_t off;  // byte offset of the pixel's (h0, w0, channel 0) in x, modulo 2^32
+    int32_t hw;    // h0 << 16 | w0 & 0xFFFF; h0 = -32768: not a pixel of this split
+};
 
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES * L::BYTES];
+template <int RS>
+__device__ __forceinline__ int row_swizzle(int p) {  // f(p) / 4
+    return RS >= 16 ? (p & 3) : RS == 8 ? ((p >> 1) & 1) : 0;
+}
+
+template <int TM, int TN, int WM, int WN, int PIX>
+struct NarrowLayout {
+    static constexpr int TK = 32 * TM * WM, TJ = 32 * TN * WN;
+    static constexpr int STAGES = 3, G = 2, TABS = 4;
+    static constexpr int X = PIX * TK * 2;          // x rows behind the dy rows
+    static constexpr int STAGE = X + PIX * TJ * 2;
+    static constexpr int RING = STAGES * STAGE;
+    static constexpr int TAB = G * RING;            // TABS tables of PIX entries per group
+    static constexpr int BYTES = TAB + G * TABS * PIX * 8;
+    static constexpr int SUMS = 256 * TM * TN * 16 * 4;
+    static_assert(BYTES <= 160 * 1024 && SUMS <= TAB, "LDS");
+};
+
+template <int TM, int TN, int WM, int WN, int PIX>
+__global__ __launch_bounds__(512, 1) void wgrad_narrow_kernel(const WgradDmaArgs ka) {
+    using L = NarrowLayout<TM, TN, WM, WN, PIX>;
+    constexpr int TK = L::TK, TJ = L::TJ, STAGES = L::STAGES, G = L::G, TABS = L::TABS;
+    constexpr int RSY = TK / 8, RSX = TJ / 8;        // segments per row
+    constexpr int PY = 64 / RSY, PX = 64 / RSX;      // rows per copy instruction
+    constexpr int NY = PIX / PY, NX = PIX / PX;      // copy instructions per stage
+    constexpr int YD = NY >= 4 ? NY / 4 : 1, XD = NX >= 4 ? NX / 4 : 1;  // ... per wave
+    constexpr int NU = PIX / 16;
+    static_assert(WM * WN == 4 && NU >= 2 && PIX <= 64, "group");
+    const WgradArgs& a = ka.a;
+
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[L::BYTES];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN;  // 0..1
-    const int wn = wave % WN;
+    const int grp = __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
+    const int wm = wave / WN, wn = wave % WN;
 
     const int K = a.K, C = a.C;
     const int J = a.R * a.S * C;
     const uint32_t PQ = (uint32_t)a.P * a.Q;
     const int64_t M = (int64_t)a.N * PQ;
-    const int64_t nchunks = (M + PIXS - 1) / PIXS;
-    const int tilesJ = (J + TILE_J - 1) / TILE_J;
-    const int tiles = tilesJ * ((K + TILE_K - 1) / TILE_K);
+    const int tilesJ = (J + TJ - 1) / TJ;
+    const int tiles = tilesJ * ((K + TK - 1) / TK);
     const int t_ = (int)xcd_remap(blockIdx.x, gridDim.x);
     const int split = t_ / tiles;
-    const int k0 = ((t_ % tiles) / tilesJ) * TILE_K;
-    const int j0 = ((t_ % tiles) % tilesJ) * TILE_J;
-    const int64_t c_begin = (int64_t)split * a.chunks_per_split;  // 64-pixel chunks
-    const int64_t c_end = min(c_begin + (int64_t)a.chunks_per_split, nchunks);
+    const int k0 = ((t_ % tiles) / tilesJ) * TK;
+    const int j0 = ((t_ % tiles) % tilesJ) * TJ;
+    // this split's pixels (ranges in 64-pixel chunks), and its group's stages; both groups run the
+    // same number (rows past the end are zeros)
+    const int64_t s_begin = (int64_t)split * a.chunks_per_split * 64;
+    const int64_t s_end = min(s_begin + (int64_t)a.chunks_per_split * 64, M);
+    const int nst = s_end > s_begin ? (int)((s_end - s_begin + G * PIX - 1) / (G * PIX)) : 0;
+    const int64_t m_begin = s_begin + (int64_t)grp * nst * PIX;
 
-    const v4i rs_dy = make_rsrc(a.dy, (uint32_t)(M * K * 2));
+    // rows of dy past the split's end are past the end of this buffer
+    const v4i rs_dy = make_rsrc(a.dy, (uint32_t)(max(s_end, (int64_t)0) * K * 2));
     const v4i rs_x = make_rsrc(a.x, (uint32_t)((int64_t)a.N * a.H * a.W * C * 2));
-    const uint32_t smem_base = lds_addr(smem);
+    uint8_t* const ring = smem + grp * L::RING;
+    const uint32_t ring_base = lds_addr(ring);
+    TapEntry* const tabs = reinterpret_cast<TapEntry*>(smem + L::TAB) + grp * TABS * PIX;
 
-    // segments this wave copies: DYQ of dy (channels k0 + 8 sg) and 4 of x (columns j0 + 8 sg)
-    int xr[4], xs[4], xc[4];
-    bool dy_ok[DYQ], x_ok[4];
-#pragma unroll
-    for (int q = 0; q < DYQ; ++q) dy_ok[q] = k0 + 8 * (DYQ * wave + q) < K;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int sg = 4 * wave + q;
-        const int j = j0 + 8 * sg;
-        x_ok[q] = j < J;
-        const int rs = x_ok[q] ? j / C : 0;
-        xc[q] = x_ok[q] ? j - rs * C : 0;
-        xr[q] = rs / a.S;
-        xs[q] = rs - xr[q] * a.S;
-    }
-    const int64_t HWC = (int64_t)a.H * a.W * C;
+    // ---- copies.  Instruction d of a stage (wave w: d = w, w + 4, ..) fills rows PY d (PX d) on;
+    //      waves with no instruction of their own repeat another's, identical bytes, so that every
+    //      wave has the same number in flight ----
+    const int yrow = PY * (wave % (NY < 4 ? NY : 4)) + lane / RSY;
+    const int xrow = PX * (wave % (NX < 4 ? NX : 4)) + lane / RSX;
+    const int yseg = (lane % RSY) ^ (4 * row_swizzle<RSY>(yrow));
+    const int xseg = (lane % RSX) ^ (4 * row_swizzle<RSX>(xrow));
+    const bool y_ok = k0 + 8 * yseg < K;
+    // a row's offset may pass 2^31 only past the buffer's end (< 2 GiB); columns past K start there
+    const uint32_t y_lane = y_ok ? (uint32_t)((m_begin + yrow) * K + k0 + 8 * yseg) * 2u : 0x80000000u;
+    const uint32_t y_step = (uint32_t)(PIX * K * 2);
+    const int jx = j0 + 8 * xseg;
+    const bool x_ok = jx < J;
+    const int tap = x_ok ? jx / C : 0;
+    const int xr = tap / a.S, xs = tap - (tap / a.S) * a.S;
+    const uint32_t x_lane = (uint32_t)((xr * a.W + xs) * C + (x_ok ? jx - tap * C : 0)) * 2u;
 
-    const int px = lane;  // lane = pixel of the stage for every DMA
-    auto issue = [&](int64_t chunk) {
-        const uint32_t st = smem_base + (uint32_t)((chunk % STAGES) * L::BYTES);
-        const int64_t m = chunk * PIXS + px;
-        const bool mok = m < M;
-        const uint32_t mm = mok ? (uint32_t)m : 0u;
-        const uint32_t img = fdiv(mm, ka.div_pq);
-        const uint32_t pq = mm - img * PQ;
-        const uint32_t p = fdiv(pq, ka.div_q);
-        const uint32_t q_ = pq - p * (uint32_t)a.Q;
-        const int h0 = (int)p * a.sh - a.ph, w0 = (int)q_ * a.sw - a.pw;
-        const uint32_t dy_row = mm * (uint32_t)K * 2u;
-        const uint32_t x_img = (uint32_t)(img * HWC);
-#pragma unroll
-        for (int q = 0; q < DYQ; ++q) {
-            const int sg = DYQ * wave + q;
-            const uint32_t off = (mok && dy_ok[q]) ? dy_row + (uint32_t)(k0 + 8 * sg) * 2u : 0x80000000u;
-            dma_b128(rs_dy, st + (uint32_t)(sg * SEG_PITCH), off);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int sg = 4 * wave + q;
-            const int h = h0 + xr[q], w = w0 + xs[q];
-            const bool ok = mok && x_ok[q] && (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W;
-            const uint32_t off = ok ? (x_img + (uint32_t)((h * a.W + w) * C + xc[q])) * 2u : 0x80000000u;
-            dma_b128(rs_x, st + (uint32_t)(OP_BYTES + sg * SEG_PITCH), off);
+    auto table = [&](int st) {  // where the taps of each pixel of stage st start
+        if (lane < PIX) {
+            const int64_t m = m_begin + (int64_t)st * PIX + lane;
+            TapEntry e = {0u, -32768 * 65536};
+            if (m < s_end) {
+                const uint32_t img = fdiv((uint32_t)m, ka.div_pq);
+                const uint32_t pq = (uint32_t)m - img * PQ;
+                const uint32_t p = fdiv(pq, ka.div_q);
+                const int h0 = (int)p * a.sh - a.ph, w0 = (int)(pq - p * (uint32_t)a.Q) * a.sw - a.pw;
+                e.off = ((img * (uint32_t)a.H + (uint32_t)h0) * (uint32_t)a.W + (uint32_t)w0) * (uint32_t)C * 2u;
+                e.hw = (int32_t)((uint32_t)h0 << 16 | ((uint32_t)w0 & 0xFFFFu));
+            }
+            tabs[(st % TABS) * PIX + lane] = e;
         }
     };
-    constexpr int kDmas = DYQ + 4;  // DMA instructions per wave per stage
+    auto issue = [&](int st, int slot) {
+        const uint32_t base = ring_base + (uint32_t)(slot * L::STAGE);
+#pragma unroll
+        for (int d = 0; d < YD; ++d) {
+            // the stage's rows in one add (wraps only where y_lane is past the end, and stays there:
+            // an offset past the buffer grows by less than 2 GiB over the whole split)
+            const uint32_t off = y_ok ? y_lane + (uint32_t)st * y_step + (uint32_t)(4 * PY * d * K * 2) : 0x80000000u;
+            dma_b128(rs_dy, base + (uint32_t)((wave % (NY < 4 ? NY : 4) + 4 * d) * 1024), off);
+        }
+#pragma unroll
+        for (int d = 0; d < XD; ++d) {
+            const TapEntry e = tabs[(st % TABS) * PIX + xrow + 4 * PX * d];
+            const int h = (e.hw >> 16) + xr, w = (int)(int16_t)e.hw + xs;
+            const bool ok = x_ok && (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W;
+            dma_b128(rs_x, base + (uint32_t)(L::X + (wave % (NX < 4 ? NX : 4) + 4 * d) * 1024),
+                     ok ? e.off + x_lane : 0x80000000u);
+        }
+    };
+    constexpr int kDmas = YD + XD;
 
-    // transposing-read addressing: lane (group g = lane / 16, i = lane % 16) reads the
-    // 8 bytes at channel 16 (g % 2) + 4 (i % 4) of pixel 8 (g / 2) + i / 4 (+ 4 for the
-    // second read) relative to the 32-channel tile and the 16-pixel step
+    // ---- operand addresses: lane (g = lane / 16, i = lane % 16) reads 8 bytes, channels
+    //      16 (g % 2) + 4 (i % 4) .. + 3 of a 32-channel tile, at pixel 8 (g / 2) + i / 4 of a step
+    //      (and + 4 in the second read) ----
     const int g = lane >> 4, i16 = lane & 15;
-    const int chl = 16 * (g & 1) + 4 * (i16 & 3);
-    const uint32_t lane_off = (uint32_t)((chl >> 3) * SEG_PITCH + (chl & 7) * 2 + (8 * (g >> 1) + (i16 >> 2)) * 16);
-    const uint32_t a_base = (uint32_t)(((wm * 128) >> 3) * SEG_PITCH) + lane_off;            // dy rows
-    const uint32_t b_base = (uint32_t)(OP_BYTES + ((wn * 64) >> 3) * SEG_PITCH) + lane_off;   // x columns
+    const int prow = 8 * (g >> 1) + (i16 >> 2);
+    const uint32_t in_tile = (uint32_t)(16 * (2 * (g & 1) + ((i16 & 3) >> 1)) + 8 * (i16 & 1));
+    uint32_t ra[STAGES][TM], rb[STAGES][TN];
+#pragma unroll
+    for (int sl = 0; sl < STAGES; ++sl) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            ra[sl][i] = (ring_base + (uint32_t)(sl * L::STAGE + prow * TK * 2 +
+                                                64 * ((wm * TM + i) ^ row_swizzle<RSY>(prow))) + in_tile) & 0x3FFFFu;
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+            rb[sl][t] = (ring_base + (uint32_t)(sl * L::STAGE + L::X + prow * TJ * 2 +
+                                                64 * ((wn * TN + t) ^ row_swizzle<RSX>(prow))) + in_tile) & 0x3FFFFu;
+    }
+    auto operand = [&](uint32_t addr, uint32_t four_rows) {
+        const v4i16 lo = read_tr(addr);
+        const v4i16 hi = read_tr(addr + four_rows);
+        typedef short v8i16 __attribute__((ext_vector_type(8)));
+        const v8i16 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf16x8, v);
+    };
+    auto load = [&](int sl, int u, bf16x8* af, bf16x8* bf) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t) bf[t] = operand(rb[sl][t] + (uint32_t)(16 * u * TJ * 2), 4 * TJ * 2);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) af[i] = operand(ra[sl][i] + (uint32_t)(16 * u * TK * 2), 4 * TK * 2);
+    };
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -201,58 +247,94 @@ __global__ __launch_bounds__(512, 1) void wgrad_seg_kernel(const WgradDmaArgs ka
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][t][v] = 0.0f;
 
+    table(wave);  // the first TABS = 4 stages, one per wave
+    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < STAGES - 1; ++c)
-        if (c_begin + c < c_end) issue(c_begin + c);
-    for (int64_t chunk = c_begin; chunk < c_end; ++chunk) {
-        // this wave's DMAs of stage `chunk` landed (later stages may still be in flight)
-        const int later = (int)min(c_end - 1 - chunk, (int64_t)(STAGES - 2));
-        wait_vmcnt(later * kDmas);
-        __syncthreads();  // ... and every other wave's; all reads of stage chunk-1 are done
-        if (chunk + STAGES - 1 < c_end) issue(chunk + STAGES - 1);  // into stage chunk-1's buffer
-        const uint32_t st = smem_base + (uint32_t)((chunk % STAGES) * L::BYTES);
-        // operands of 16-pixel step u + 1 are read while the MFMAs of step u run
-        bf16x8 af[2][TM], bf[2][TN];
-        auto load = [&](int u, int b) {
+    for (int c = 0; c < STAGES; ++c)
+        if (c < nst) issue(c, c);
+    auto wait_stage = [&](int x) {  // stage x landed; up to STAGES - 1 later ones may be in flight
+        const int later = min(nst - 1 - x, STAGES - 1);
+        if (later >= 2)
+            wait_vmcnt(2 * kDmas);
+        else if (later == 1)
+            wait_vmcnt(kDmas);
+        else
+            wait_vmcnt(0);
+    };
+    bf16x8 af[2][TM], bf[2][TN];
+    if (nst > 0) {
+        wait_stage(0);
+        __syncthreads();
+        load(0, 0, af[0], bf[0]);
+    }
+    auto stage = [&](int it, auto slot) {
+        constexpr int SL = decltype(slot)::value;
+        constexpr int SN = SL + 1 == STAGES ? 0 : SL + 1;
 #pragma unroll
-            for (int i = 0; i < TM; ++i) af[b][i] = operand(st + a_base + (uint32_t)(4 * i * SEG_PITCH + u * 256));
-#pragma unroll
-            for (int t = 0; t < TN; ++t) bf[b][t] = operand(st + b_base + (uint32_t)(4 * t * SEG_PITCH + u * 256));
-        };
-        load(0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < PIXS / 16; ++u) {
-            if (u + 1 < PIXS / 16) load(u + 1, (u + 1) & 1);
+        for (int u = 0; u < NU; ++u) {
+            if (u + 1 < NU) {
+                load(SL, u + 1, af[(u + 1) & 1], bf[(u + 1) & 1]);
+            } else {
+                // stages 0 .. it + STAGES - 1 are issued
+                if (it + STAGES - 1 < nst)
+                    wait_vmcnt((STAGES - 2) * kDmas);
+                else
+                    wait_vmcnt(0);
+                __syncthreads();
+                if (it + STAGES < nst) issue(it + STAGES, SL);
+                if (wave == (it & 3) && it + STAGES + 1 < nst) table(it + STAGES + 1);
+                load(SN, 0, af[(u + 1) & 1], bf[(u + 1) & 1]);  // unused after the last stage
+            }
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int t = 0; t < TN; ++t) acc[i][t] = mfma32(af[u & 1][i], bf[u & 1][t], acc[i][t]);
-            if (u + 1 < PIXS / 16) interleave_reads();
             __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    static_assert(NU % 2 == 0 && STAGES == 3, "operand sets alternate, ring unrolled over three slots");
+    for (int it = 0; it < nst; it += STAGES) {
+        stage(it, std::integral_constant<int, 0>{});
+        if (it + 1 < nst) stage(it + 1, std::integral_constant<int, 1>{});
+        if (it + 2 < nst) stage(it + 2, std::integral_constant<int, 2>{});
     }
 
+    // ---- group 1 hands its sums over (16-byte pieces, lane-contiguous) ----
+    __syncthreads();
+    f32x4* const xch = reinterpret_cast<f32x4*>(smem) + wave * 64 + lane;
+    if (grp == 1) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    xch[((i * TN + t) * 4 + v) * 256] =
+                        f32x4{acc[i][t][4 * v], acc[i][t][4 * v + 1], acc[i][t][4 * v + 2], acc[i][t][4 * v + 3]};
+    }
+    __syncthreads();
+    if (grp == 1) return;  // no barrier follows
     float* out = a.out + (int64_t)split * K * J;
     const int l32 = lane & 31, half = lane >> 5;
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
         const int col = j0 + wn * 32 * TN + 32 * t + l32;
-        if (col >= J) continue;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = k0 + wm * 128 + 32 * i + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (row < K) {
+                const int row = k0 + wm * 32 * TM + 32 * i + 8 * (v >> 2) + 4 * half + (v & 3);
+                if (row < K && col < J) {
                     float* o = out + (int64_t)row * J + col;
-                    *o = a.accumulate ? *o + acc[i][t][v] : acc[i][t][v];
+                    const float s = acc[i][t][v] + xch[((i * TN + t) * 4 + (v >> 2)) * 256][v & 3];
+                    *o = a.accumulate ? *o + s : s;
                 }
             }
+        }
     }
 }
 
-// Pixel-major variant: a stage holds PIXR pixels of the dy tile (256 channels, 512 bytes)
+// Wide variant: a stage holds PIXR pixels of the dy tile (256 channels, 512 bytes)
 // then the same pixels of the x tile (256 columns).  Pixel rows are stored in pairs:
 // pixels i and i + PIXR/2 of the stage share a 1088-byte slot (512 + 512 + 64 bytes of
 // padding), so one DMA instruction with all 64 lanes active copies two pixels (each lane
@@ -659,16 +741,29 @@ bool wgrad_dma_eligible(const WgradArgs& a) {
     return a.C % 8 == 0 && a.K % 8 == 0 && M * a.K * 2 < 0x7FFFFFF0ll && xbytes < 0x7FFFFFF0ll;
 }
 
-WgradDmaPlan wgrad_dma_plan(int K, int J) {
+WgradDmaPlan wgrad_dma_plan(const WgradArgs& a) {
     WgradDmaPlan p;
-    // pixel-major rows for wide layers; the segment-major stages waste less of the
-    // 256-row tile's copy work when K is narrow
-    p.cfg = K >= 128 ? 1 : 0;
+    const int K = a.K, J = a.R * a.S * a.C;
     const int forced = knob(KNOB_WGRAD_CFG);
-    if (forced == 0 || forced == 1) p.cfg = forced;
-    p.tiles = ((K + TILE_K - 1) / TILE_K) * ((J + 255) / 256);
+    const bool narrow_ok = a.H + a.ph <= 32767 && a.W + a.pw <= 32767 && a.ph <= 32767 && a.pw <= 32767;
+    p.tk = p.tj = 256;
+    // Narrow tiles up to 128 filters or 64 columns, against 256 x 256 ones (graph-replayed, with the
+    // reduction of the partials): 32 x 32 x 128 -> 128 3 x 3 at batch 128 60 against 76 us, 56 x 56 x 64
+    // -> 64 at batch 64 43 / 65, 36 x 39 x 384 -> 24 at batch 135 114 / 224, 1 x 1 8 -> 354 over 127 k
+    // pixels 57 / 70; the segment-major kernel they replace (64-pixel stages, one 16-byte piece of 64
+    // different rows per copy) took 80, 74, 276 and 83 us.
+    if (narrow_ok && (forced == 0 || (forced != 1 && (K <= 128 || J <= 64)))) {
+        if (J <= 64) {
+            p.tj = 64;
+            p.tk = K <= 64 ? 64 : 256;
+        } else {
+            p.tk = K <= 32 ? 32 : K <= 64 ? 64 : 128;
+        }
+    }
+    p.cfg = p.tk == 256 && p.tj == 256 ? 1 : 0;
+    p.tiles = ((K + p.tk - 1) / p.tk) * ((J + p.tj - 1) / p.tj);
     p.resident_blocks = 256;  // one block per CU
-    // pixel-major kernel: 48-pixel stages in a three-deep ring (measured best of 32 / 48 / 64)
+    // wide kernel: 48-pixel stages in a three-deep ring (measured best of 32 / 48 / 64)
     p.pix = 48;
     const int px = knob(KNOB_WGRAD_PIX);
     if (px == 32 || px == 64) p.pix = px;
@@ -699,7 +794,7 @@ hipError_t launch_wgrad_dma(const WgradArgs& a, hipStream_t stream) {
     // turns it on
     const int pf = knob(KNOB_WGRAD_PF);
     ka.pf_dist = pf > 0 ? pf : 0;
-    const WgradDmaPlan p = wgrad_dma_plan(a.K, a.R * a.S * a.C);
+    const WgradDmaPlan p = wgrad_dma_plan(a);
     const dim3 grid((unsigned)(p.tiles * a.splits));
     if (p.cfg == 1) {
         // linear copy addressing: stride 1, output the input's size, whole 256-column
@@ -709,8 +804,16 @@ hipError_t launch_wgrad_dma(const WgradArgs& a, hipStream_t stream) {
             launch_rows<true>(p.pix, ka.pf_dist > 0, grid, ka, stream);
         else
             launch_rows<false>(p.pix, ka.pf_dist > 0, grid, ka, stream);
+    } else if (p.tj == 64 && p.tk == 64) {
+        hipLaunchKernelGGL((wgrad_narrow_kernel<1, 1, 2, 2, 64>), grid, dim3(512), 0, stream, ka);
+    } else if (p.tj == 64) {
+        hipLaunchKernelGGL((wgrad_narrow_kernel<2, 2, 4, 1, 32>), grid, dim3(512), 0, stream, ka);
+    } else if (p.tk == 32) {
+        hipLaunchKernelGGL((wgrad_narrow_kernel<1, 2, 1, 4, 32>), grid, dim3(512), 0, stream, ka);
+    } else if (p.tk == 64) {
+        hipLaunchKernelGGL((wgrad_narrow_kernel<2, 2, 1, 4, 32>), grid, dim3(512), 0, stream, ka);
     } else {
-        hipLaunchKernelGGL(wgrad_seg_kernel, grid, dim3(512), 0, stream, ka);
+        hipLaunchKernelGGL((wgrad_narrow_kernel<4, 2, 1, 4, 32>), grid, dim3(512), 0, stream, ka);
     }
     return hipGetLastError();
 }
