@@ -127,6 +127,11 @@ struct ConvPadPlan {
 bool conv_pad_plan(const ConvGemmArgs& a, ConvPadPlan* p);
 hipError_t launch_conv_padded(const ConvGemmArgs& a, const ConvPadPlan& p, void* ws, hipStream_t stream);
 
+// Few output rows (operands and limits of the LDS-DMA kernel): the shape (51-55) with which the
+// small-layer kernel runs this layer, 0 where the tiled kernel does; cfg in 51-55 forces one.
+int conv_small_cfg(const ConvGemmArgs& a, int cfg);
+hipError_t launch_conv_small(const ConvGemmArgs& a, int cfg, hipStream_t stream);
+
 // Forward pass for inputs with few channels (C < 8 bf16, or fp32 with C <= 8): input patch
 // and decoded filters staged in LDS with the channels padded to a power of two.
 struct ThinGeom {
