@@ -426,17 +426,16 @@ tbn_status tbn_conv2d_bwd_data(const tbn_conv_desc* desc, const void* dy, const 
     if (!aligned16(ws)) return fail(TBN_ERR_ALIGN, "workspace must be 16-byte aligned");
     uint32_t* codes_t = reinterpret_cast<uint32_t*>(ws);
     uint32_t* apair = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(ws) + w.apair_off);
-    hipError_t e = tbn::launch_repack_bwd(codes, alpha, (int32_t)gg.K, (int32_t)g.K, (int32_t)g.R, (int32_t)g.S,
-                                          (int32_t)g.C, codes_t, apair, stream);
-    if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_data (repack)");
     const void* dyk = dy;
+    tbn::PadArgs pad = {};
     if (padk) {
-        uint16_t* dyp = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(ws) + dy_off);
-        e = tbn::launch_pad_channels(reinterpret_cast<const uint16_t*>(dy), g.N * g.P * g.Q, (int32_t)g.K,
-                                     (int32_t)gk.K, dyp, stream);
-        if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_data (channel copy)");
+        void* const dyp = reinterpret_cast<char*>(ws) + dy_off;
+        pad = tbn::make_pad(dy, g.N * g.P * g.Q, (int32_t)g.K, (int32_t)gk.K, dyp);
         dyk = dyp;
     }
+    hipError_t e = tbn::launch_repack_bwd(codes, alpha, (int32_t)gg.K, (int32_t)g.K, (int32_t)g.R, (int32_t)g.S,
+                                          (int32_t)g.C, codes_t, apair, pad, stream);
+    if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_data (repack)");
     tbn::ConvGemmArgs a = bwd_data_args(gg, dxt);
     a.x = dyk;
     a.codes = codes_t;
@@ -465,24 +464,23 @@ tbn_status tbn_conv2d_bwd_weight(const tbn_conv_desc* desc, const void* x, const
         tbn::WgradArgs a = wgrad_args(gp);
         a.x = reinterpret_cast<const uint16_t*>(x);
         a.dy = reinterpret_cast<const uint16_t*>(dy);
+        tbn::PadArgs px = {}, pdy = {};
         if (gp.C != g.C) {
-            uint16_t* const xp = reinterpret_cast<uint16_t*>(base);
-            hipError_t e = tbn::launch_pad_channels(a.x, g.N * g.H * g.W, (int32_t)g.C, (int32_t)gp.C, xp, stream);
-            if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
-            a.x = xp;
+            px = tbn::make_pad(x, g.N * g.H * g.W, (int32_t)g.C, (int32_t)gp.C, base);
+            a.x = px.xp;
         }
         if (gp.K != g.K) {
-            uint16_t* const dyp = reinterpret_cast<uint16_t*>(base + wp.dy_off);
-            hipError_t e = tbn::launch_pad_channels(a.dy, g.N * g.P * g.Q, (int32_t)g.K, (int32_t)gp.K, dyp, stream);
-            if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
-            a.dy = dyp;
+            pdy = tbn::make_pad(dy, g.N * g.P * g.Q, (int32_t)g.K, (int32_t)gp.K, base + wp.dy_off);
+            a.dy = pdy.xp;
         }
+        hipError_t e = tbn::launch_pad_channels(px, pdy, stream);
+        if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight (channel copy)");
         a.out = part;
         const int64_t chunks = (g.N * g.P * g.Q + 63) / 64;
         a.splits = wp.splits;
         a.chunks_per_split = (int32_t)((chunks + wp.splits - 1) / wp.splits);
         a.accumulate = 0;
-        hipError_t e = tbn::launch_wgrad(a, stream);
+        e = tbn::launch_wgrad(a, stream);
         if (e != hipSuccess) return hip_fail(e, "tbn_conv2d_bwd_weight");
         const int64_t rows = g.K * g.R * g.S, stride = gp.K * g.R * g.S * gp.C;
         e = gp.C != g.C ? tbn::launch_split_reduce_compact(part, wp.splits, rows, stride, (int32_t)g.C, (int32_t)gp.C, dw,

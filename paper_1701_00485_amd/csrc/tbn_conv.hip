@@ -310,70 +310,6 @@ hipError_t launch_mode(const ConvGemmArgs& a, int cfg, hipStream_t stream) {
     return launch_cfg<128, 128, 64, 64, AM, BWD>(a, stream);
 }
 
-// ---------------- backward-data operand preparation ----------------
-// K may exceed the layer's Kreal filters (a gradient padded to a multiple of 8 channels):
-// filters k >= Kreal read the zero padding bits of the last 64-filter block and get scale 0.
-__global__ __launch_bounds__(256) void repack_bwd_kernel(const uint32_t* __restrict__ codes,
-                                                         const float* __restrict__ alpha, int32_t K, int32_t Kreal,
-                                                         int32_t R, int32_t S, int32_t C,
-                                                         uint32_t* __restrict__ codes_t,
-                                                         uint32_t* __restrict__ apair) {
-    // every count below is < 2^31 (R*S*C and R*S*K < 2^30, checked by the host)
-    const uint32_t n = (uint32_t)(R * S * C);     // elements of a forward filter
-    const uint32_t nt = (uint32_t)(R * S * K);    // elements of a transposed filter
-    const uint32_t nb = (n + 63) / 64;
-    const uint32_t nbt = (nt + 63) / 64;
-    const uint32_t cb = (uint32_t)(C + 63) / 64;
-    const int64_t words = (int64_t)cb * nbt * 256;
-    const int64_t pairs = (int64_t)nbt * 32;
-    const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (gid < words) {
-        const uint32_t g32 = (uint32_t)gid;
-        const uint32_t wsub = g32 & 3;
-        const uint32_t cc = (g32 >> 2) & 63;
-        const uint32_t eb = (g32 >> 8) % nbt;
-        const uint32_t cblk = (g32 >> 8) / nbt;
-        const uint32_t c = cblk * 64 + cc;
-        uint32_t word = 0;
-        uint32_t et = eb * 64 + wsub * 16;  // first (r', s', k) of the flipped filter in this word
-        if (c < (uint32_t)C && et < nt) {
-            // walk k, carrying into s' and r' (one division per word, none per element)
-            uint32_t k = et % (uint32_t)K, rs = et / (uint32_t)K;
-            uint32_t rp = rs / (uint32_t)S, sp = rs - rp * (uint32_t)S;
-            for (int e = 0; e < 16 && et < nt; ++e, ++et) {
-                const uint32_t i = ((R - 1 - rp) * S + (S - 1 - sp)) * C + c;  // element of forward filter k
-                const uint32_t src = codes[(((k >> 6) * nb + (i >> 6)) * 64 + (k & 63)) * 4 + ((i & 63) >> 4)];
-                const int ei = (int)(i & 15), hi = ei & 1, j = ei >> 1;
-                const uint32_t mag = (src >> (16 * hi + j)) & 1u;
-                const uint32_t neg = (src >> (16 * hi + 8 + j)) & 1u;
-                const int eh = e & 1, ej = e >> 1;
-                word |= (mag << (16 * eh + ej)) | (neg << (16 * eh + 8 + ej));
-                if (++k == (uint32_t)K) {
-                    k = 0;
-                    if (++sp == (uint32_t)S) {
-                        sp = 0;
-                        ++rp;
-                    }
-                }
-            }
-        }
-        codes_t[gid] = word;
-    }
-    if (gid < pairs) {
-        uint32_t v = 0;
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t et = 2 * (uint32_t)gid + h;
-            if (et < nt) {
-                const uint32_t kk = et % (uint32_t)K;
-                uint32_t b = kk < (uint32_t)Kreal ? f32_to_bf16_bits(alpha[kk]) : 0u;
-                if ((b & 0x7F80u) == 0) b = 0;  // a denormal scale is flushed: exponent + 1 would not double it
-                v |= b << (16 * h);
-            }
-        }
-        apair[gid] = v;
-    }
-}
-
 }  // namespace
 
 // Tile-shape and split overrides for tuning and for the tests that cover every shape (the
@@ -446,8 +382,8 @@ bool conv_pad_plan(const ConvGemmArgs& a, ConvPadPlan* p) {
 hipError_t launch_conv_padded(const ConvGemmArgs& a, const ConvPadPlan& p, void* ws, hipStream_t stream) {
     uint8_t* const base = reinterpret_cast<uint8_t*>(ws);
     uint32_t* const codes_p = reinterpret_cast<uint32_t*>(base + p.codes_off);
-    hipError_t e = launch_pad_fwd(a.x, a.x_f32, (int64_t)a.N * a.H * a.W, a.C, p.Cp, base, a.codes, a.Kf, a.R * a.S,
-                                  codes_p, stream);
+    hipError_t e = launch_pad_fwd(make_pad(a.x, (int64_t)a.N * a.H * a.W, a.C, p.Cp, base), a.x_f32, a.codes, a.Kf,
+                                  a.R * a.S, codes_p, stream);
     if (e != hipSuccess) return e;
     ConvGemmArgs b = padded_args(a, p.Cp);
     b.x = base;
@@ -476,17 +412,6 @@ hipError_t launch_conv_gemm(const ConvGemmArgs& args, hipStream_t stream) {
     const bool vec = (a.C % 8 == 0) && !a.x_f32;
     if (a.apair) return vec ? launch_mode<A_VEC8, true>(a, cfg, stream) : launch_mode<A_SCALAR, true>(a, cfg, stream);
     return vec ? launch_mode<A_VEC8, false>(a, cfg, stream) : launch_mode<A_SCALAR, false>(a, cfg, stream);
-}
-
-hipError_t launch_repack_bwd(const uint32_t* codes, const float* alpha, int32_t K, int32_t Kreal, int32_t R,
-                             int32_t S, int32_t C, uint32_t* codes_t, uint32_t* apair, hipStream_t stream) {
-    const int64_t nt = (int64_t)R * S * K;
-    const int64_t nbt = (nt + 63) / 64;
-    const int64_t words = (int64_t)((C + 63) / 64) * nbt * 256;
-    const int64_t total = words > nbt * 32 ? words : nbt * 32;
-    hipLaunchKernelGGL(repack_bwd_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, codes,
-                       alpha, K, Kreal, R, S, C, codes_t, apair);
-    return hipGetLastError();
 }
 
 }  // namespace tbn

@@ -165,13 +165,6 @@ struct FcStreamPlan {
 bool fc_stream_plan(const ConvGemmArgs& a, FcStreamPlan* p);
 hipError_t launch_fc_stream(const ConvGemmArgs& a, const FcStreamPlan& p, hipStream_t stream);
 
-// Re-pack the codes of K filters [K][R][S][C] into the codes of the C filters of the
-// transposed, spatially flipped layer [C][R][S][K] (backward-data operand), and build
-// the bf16 scale pairs of that layer's element pairs; filters Kreal..K-1 (channel padding
-// of the gradient) get scale 0.
-hipError_t launch_repack_bwd(const uint32_t* codes, const float* alpha, int32_t K, int32_t Kreal, int32_t R,
-                             int32_t S, int32_t C, uint32_t* codes_t, uint32_t* apair, hipStream_t stream);
-
 struct WgradArgs {
     const uint16_t* x;        // NHWC [N][H][W][C] bf16
     const uint16_t* dy;       // NHWC [N][P][Q][K] bf16
@@ -216,10 +209,29 @@ struct RepackFwdArgs {
     uint32_t nbp;
     FastDiv div_cp, div_nbp;
 };
-hipError_t launch_pad_channels(const uint16_t* x, int64_t pixels, int32_t C, int32_t Cp, uint16_t* xp,
-                               hipStream_t stream);
-hipError_t launch_pad_fwd(const void* x, int x_f32, int64_t pixels, int32_t C, int32_t Cp, void* xp,
-                          const uint32_t* codes, int32_t K, int32_t taps, uint32_t* codes_p, hipStream_t stream);
+struct RepackBwdArgs {
+    const uint32_t* codes;
+    const float* alpha;
+    uint32_t* codes_t;
+    uint32_t* apair;
+    int64_t words, pairs;  // of codes_t, of apair
+    int32_t K, Kreal, R, S, C;
+    uint32_t nb, nt, nbt;
+    FastDiv div_k, div_nbt;
+};
+PadArgs make_pad(const void* x, int64_t pixels, int32_t C, int32_t Cp, void* xp);
+// one or two bf16 tensors (an empty PadArgs: none)
+hipError_t launch_pad_channels(const PadArgs& a, const PadArgs& b, hipStream_t stream);
+// a tensor (bf16 or fp32) and the codes of K filters of `taps` taps over its channels
+hipError_t launch_pad_fwd(const PadArgs& a, int x_f32, const uint32_t* codes, int32_t K, int32_t taps,
+                          uint32_t* codes_p, hipStream_t stream);
+// Re-pack the codes of K filters [K][R][S][C] into the codes of the C filters of the
+// transposed, spatially flipped layer [C][R][S][K] (backward-data operand), and build
+// the bf16 scale pairs of that layer's element pairs; filters Kreal..K-1 (channel padding
+// of the gradient) get scale 0.  `dy`: the gradient's channel copy, made by the same launch.
+hipError_t launch_repack_bwd(const uint32_t* codes, const float* alpha, int32_t K, int32_t Kreal, int32_t R,
+                             int32_t S, int32_t C, uint32_t* codes_t, uint32_t* apair, const PadArgs& dy,
+                             hipStream_t stream);
 // partials [splits][stride] of a Cp-channel filter gradient, channels c < C of the first
 // `rows` rows kept: dw[row][c] (+)= sum_z
 hipError_t launch_split_reduce_compact(const float* partials, int32_t splits, int64_t rows, int64_t stride, int32_t C,

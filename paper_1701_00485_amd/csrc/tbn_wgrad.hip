@@ -241,103 +241,92 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
     dw[i] = s;
 }
 
-// The same sum, four consecutive outputs per thread with 16-byte loads (count and stride
-// multiples of 4, 16-byte aligned arrays): a quarter of the load instructions for the
-// memory-bound pass over all partials.  Each output adds its partials in split order, as
-// above, so the results are identical.
+// The same sum, four consecutive outputs per thread with 16-byte loads (16-byte aligned arrays,
+// stride a multiple of 4), `count4` such groups; G threads per group add every G-th split and are
+// combined in order (fixed, so the result is the same on every run).  With few outputs and many
+// splits (first layers, narrow layers) one thread each would leave the chip idle on a long chain.
+// The partials' rows have Cp channels, of which the first C are kept (C = Cp: flat).
+template <int G, bool COMPACT>
 __global__ __launch_bounds__(256) void split_reduce_vec4_kernel(const float* __restrict__ part, int32_t splits,
-                                                                int64_t count, int64_t stride, float* __restrict__ dw,
+                                                                int64_t count4, int64_t stride, int32_t C, int32_t Cp,
+                                                                FastDiv div_cp, float* __restrict__ dw,
                                                                 int32_t accumulate) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= count) return;
-    f32x4 s = accumulate ? *reinterpret_cast<const f32x4*>(dw + i) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    int z = 0;
-    for (; z + 8 <= splits; z += 8) {
-        f32x4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(part + (int64_t)(z + u) * stride + i);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; z < splits; ++z) s += *reinterpret_cast<const f32x4*>(part + (int64_t)z * stride + i);
-    *reinterpret_cast<f32x4*>(dw + i) = s;
-}
-
-// Few outputs with many splits (first layers: K x R*S*C of a few thousand): G threads
-// per output each add every G-th split, then the G sums are added in group order (fixed,
-// so the result is the same on every run).
-template <int G>
-__global__ __launch_bounds__(256) void split_reduce_groups_kernel(const float* __restrict__ part,
-                                                                  int32_t splits, int64_t count, int64_t stride,
-                                                                  float* __restrict__ dw, int32_t accumulate) {
-    constexpr int OPB = 256 / G;  // outputs per block
-    __shared__ float sh[256];
+    constexpr int OPB = 256 / G;  // groups of four per block
+    __shared__ f32x4 sh[G > 1 ? 256 : 1];
     const int o = threadIdx.x % OPB, g = threadIdx.x / OPB;
-    const int64_t i = (int64_t)blockIdx.x * OPB + o;
-    float s = 0.0f;
-    if (i < count)
-        for (int z = g; z < splits; z += G) s += part[(int64_t)z * stride + i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    if (g == 0 && i < count) {
-        float t = accumulate ? dw[i] : 0.0f;
-        for (int gg = 0; gg < G; ++gg) t += sh[gg * OPB + o];
-        dw[i] = t;
+    const int64_t i4 = (int64_t)blockIdx.x * OPB + o, i = i4 * 4;
+    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+    float* out = dw + i;
+    int keep = 4;  // of the four outputs
+    if constexpr (COMPACT) {
+        const int64_t row = count4 < 0x1FFFFFFF ? (int64_t)fdiv((uint32_t)i, div_cp) : i / Cp;
+        const int c = (int)(i - row * Cp);
+        keep = max(0, min(4, C - c));
+        out = dw + row * C + c;
     }
-}
-
-// Sum of the split partials of a channel-padded filter gradient [splits][stride] with rows of
-// Cp channels, keeping channels c < C: dw[row][c] (+)= sum_z part[z][row][c], G threads per
-// output adding every G-th split (eight loads in flight where one thread adds them all),
-// combined in group order (fixed).
-template <int G>
-__global__ __launch_bounds__(256) void split_reduce_compact_kernel(const float* __restrict__ part, int32_t splits,
-                                                                   int64_t rows, int64_t stride, int32_t C, int32_t Cp,
-                                                                   FastDiv div_c, float* __restrict__ dw,
-                                                                   int32_t accumulate) {
-    constexpr int OPB = 256 / G;
-    __shared__ float sh[256];
-    const int o = threadIdx.x % OPB, g = threadIdx.x / OPB;
-    const int64_t i = (int64_t)blockIdx.x * OPB + o;  // output (row, c)
-    const int64_t count = rows * C;
-    const int64_t row = count < 0x7FFFFFFF ? (int64_t)fdiv((uint32_t)i, div_c) : i / C;
-    const int64_t src = row * Cp + (i - row * C);
-    float s = 0.0f;
-    if (i < count) {
+    if (i4 < count4 && keep > 0) {
+        if (G == 1 && !COMPACT && accumulate) s = *reinterpret_cast<const f32x4*>(out);
+        const float* p = part + (int64_t)g * stride + i;
         int z = g;
-        if constexpr (G == 1) {
-            for (; z + 8 <= splits; z += 8) {
-                float v[8];
+        for (; z + 7 * G < splits; z += 8 * G, p += 8 * G * stride) {
+            f32x4 v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(z + u) * stride + src];
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4*>(p + (int64_t)u * G * stride);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s += v[u];
-            }
+            for (int u = 0; u < 8; ++u) s += v[u];
         }
-        for (; z < splits; z += G) s += part[(int64_t)z * stride + src];
+        // the rest together: past the end re-read the last split and add nothing
+        f32x4 v[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            v[u] = z + u * G < splits ? *reinterpret_cast<const f32x4*>(p + (int64_t)u * G * stride)
+                                      : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (z + u * G < splits) s += v[u];
     }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    if (g == 0 && i < count) {
-        float t = accumulate ? dw[i] : 0.0f;
-        for (int gg = 0; gg < G; ++gg) t += sh[gg * OPB + o];
-        dw[i] = t;
+    if constexpr (G > 1) {
+        sh[threadIdx.x] = s;
+        __syncthreads();
+        if (g > 0) return;
+#pragma unroll
+        for (int gg = 1; gg < G; ++gg) s += sh[gg * OPB + o];
     }
+    if (i4 >= count4) return;
+    if constexpr (COMPACT) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < keep) out[e] = accumulate ? out[e] + s[e] : s[e];
+    } else {
+        if (G > 1 && accumulate) s += *reinterpret_cast<const f32x4*>(out);
+        *reinterpret_cast<f32x4*>(out) = s;
+    }
+}
+
+template <bool COMPACT>
+hipError_t launch_vec4(const float* part, int32_t splits, int64_t count4, int64_t stride, int32_t C, int32_t Cp,
+                       float* dw, int32_t accumulate, hipStream_t stream) {
+    const FastDiv div_cp = make_fastdiv((uint32_t)Cp);
+    // enough threads to fill the chip, at least two splits each
+    const int G = count4 >= 65536 || splits < 8 ? 1 : count4 >= 16384 || splits < 32 ? 4 : 16;
+    const dim3 grid((unsigned)((count4 * G + 255) / 256));
+    if (G == 1)
+        hipLaunchKernelGGL((split_reduce_vec4_kernel<1, COMPACT>), grid, dim3(256), 0, stream, part, splits, count4,
+                           stride, C, Cp, div_cp, dw, accumulate);
+    else if (G == 4)
+        hipLaunchKernelGGL((split_reduce_vec4_kernel<4, COMPACT>), grid, dim3(256), 0, stream, part, splits, count4,
+                           stride, C, Cp, div_cp, dw, accumulate);
+    else
+        hipLaunchKernelGGL((split_reduce_vec4_kernel<16, COMPACT>), grid, dim3(256), 0, stream, part, splits, count4,
+                           stride, C, Cp, div_cp, dw, accumulate);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_split_reduce_compact(const float* partials, int32_t splits, int64_t rows, int64_t stride, int32_t C,
                                        int32_t Cp, float* dw, int32_t accumulate, hipStream_t stream) {
-    const int64_t count = rows * C;
-    const FastDiv div_c = make_fastdiv((uint32_t)C);
-    if (count < 65536 && splits >= 32)
-        hipLaunchKernelGGL(split_reduce_compact_kernel<16>, dim3((unsigned)((count + 15) / 16)), dim3(256), 0, stream,
-                           partials, splits, rows, stride, C, Cp, div_c, dw, accumulate);
-    else
-        hipLaunchKernelGGL(split_reduce_compact_kernel<1>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream,
-                           partials, splits, rows, stride, C, Cp, div_c, dw, accumulate);
-    return hipGetLastError();
+    return launch_vec4<true>(partials, splits, rows * Cp / 4, stride, C, Cp, dw, accumulate, stream);
 }
 
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t stream) {
@@ -358,12 +347,8 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t stream) {
 
 hipError_t launch_split_reduce(const float* partials, int32_t splits, int64_t count, int64_t stride, float* dw,
                                int32_t accumulate, hipStream_t stream) {
-    if (count < 65536 && splits >= 32) {
-        hipLaunchKernelGGL(split_reduce_groups_kernel<16>, dim3((unsigned)((count + 15) / 16)), dim3(256), 0, stream,
-                           partials, splits, count, stride, dw, accumulate);
-    } else if (count % 4 == 0 && stride % 4 == 0 && (((uintptr_t)partials | (uintptr_t)dw) & 15) == 0) {
-        hipLaunchKernelGGL(split_reduce_vec4_kernel, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, stream,
-                           partials, splits, count, stride, dw, accumulate);
+    if (count % 4 == 0 && stride % 4 == 0 && (((uintptr_t)partials | (uintptr_t)dw) & 15) == 0) {
+        return launch_vec4<false>(partials, splits, count / 4, stride, 4, 4, dw, accumulate, stream);
     } else {
         hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream,
                            partials, splits, count, stride, dw, accumulate);
