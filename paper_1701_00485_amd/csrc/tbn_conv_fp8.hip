@@ -24,6 +24,7 @@
 //     stores bf16 or fp32 through an LDS staging tile with 16-byte stores.
 //
 // M0 is written by the DMA helper; nothing else in these kernels uses M0.
+#include "tbn_codes8.h"
 #include "tbn_device.h"
 #include "tbn_dma.h"
 #include "tbn_kernels.h"
@@ -41,35 +42,6 @@ struct Fp8Layout {
     static constexpr int B = BM * ROWB;    // code chunk 0 of the BN filters, then chunk 1
     static constexpr int BYTES = B + 2 * BN * 16;
 };
-
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-// D += A B with A the E2M1 filter operand (format 4) and B the E4M3 activation operand
-// (format 0), both scales 2^0 (E8M0 code 127)
-__device__ __forceinline__ f32x16 mfma_f4f8(i32x8 fil, i32x8 act, f32x16 c) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fil, act, c, 4, 0, 0, 127, 0, 127);
-}
-
-// (t << 1) + c in one v_lshl_add_u32 (c in a scalar register: the three-operand form takes
-// no literal)
-__device__ __forceinline__ uint32_t shl1_add(uint32_t t, uint32_t c) {
-    uint32_t r;
-    asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(r) : "v"(t), "s"(c));
-    return r;
-}
-
-// The 32 E2M1 values of words w0 (elements 0..15) and w1 (16..31) of the repacked layout;
-// two22 = 0x22222222 (the 2 of every nibble) in a scalar register.
-__device__ __forceinline__ i32x8 decode_f4(uint32_t w0, uint32_t w1, uint32_t two22) {
-    i32x4 r;
-    r[0] = (int)((w0 & 0xAAAAAAAAu) + two22);
-    r[1] = (int)shl1_add(w0 & 0x55555555u, two22);
-    r[2] = (int)((w1 & 0xAAAAAAAAu) + two22);
-    r[3] = (int)shl1_add(w1 & 0x55555555u, two22);
-    // the E2M1 form reads only the low four dwords: the others are left undefined
-    return __builtin_shufflevector(r, r, 0, 1, 2, 3, -1, -1, -1, -1);
-}
 
 // UNI: C % 128 == 0, so all 128 elements of a stage share one tap (r, s) and the tap
 // bookkeeping is wave-uniform.  Otherwise C % 16 == 0 and every lane tracks the tap of its
@@ -488,13 +460,8 @@ bool conv_fp8_eligible(const ConvFp8Args& a) {
 
 int conv_fp8_tile(const ConvFp8Args& a) {
     const int forced = knob(KNOB_FP8_TILE);
-    if (forced >= 1 && forced <= 4) return forced;
-    const int64_t M = (int64_t)a.N * a.P * a.Q;
-    int cfg = a.K > 128 ? 1 : (a.K > 64 ? 2 : 3);
-    const int bm = 128, bn = cfg == 1 ? 256 : (cfg == 2 ? 128 : 64);
-    // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles
-    if (((M + bm - 1) / bm) * ((a.K + bn - 1) / bn) < 384 && a.K >= 128) cfg = 4;
-    return cfg;
+    if (forced >= 1 && forced <= 8) return forced;
+    return conv_code8_tile(a.N, a.P, a.Q, a.K, (int64_t)a.R * a.S * a.C);
 }
 
 hipError_t launch_conv_fp8(const ConvFp8Args& args, hipStream_t stream) {
@@ -502,7 +469,9 @@ hipError_t launch_conv_fp8(const ConvFp8Args& args, hipStream_t stream) {
     ConvFp8Args a = args;
     a.div_q = make_fastdiv((uint32_t)a.Q);
     a.div_pq = make_fastdiv((uint32_t)a.P * (uint32_t)a.Q);
-    switch (conv_fp8_tile(a)) {
+    const int tile = conv_fp8_tile(a);
+    if (tile >= 5) return launch_conv_fp8_small(a, tile, stream);
+    switch (tile) {
         case 2: return launch_fp8_cfg<128, 128, 2, 2, 3>(a, stream);
         case 3: return launch_fp8_cfg<128, 64, 2, 2, 3>(a, stream);
         case 4: return launch_fp8_cfg<64, 128, 1, 4, 4>(a, stream);

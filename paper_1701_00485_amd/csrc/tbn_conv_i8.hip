@@ -24,6 +24,7 @@
 // M0 is written by the DMA helper; nothing else in these kernels uses M0.
 #include <cstdlib>
 
+#include "tbn_codes8.h"
 #include "tbn_device.h"
 #include "tbn_dma.h"
 #include "tbn_kernels.h"
@@ -41,32 +42,6 @@ struct I8Layout {
     static constexpr int B = BM * ROWB;    // code chunk 0 of the BN filters, then chunk 1
     static constexpr int BYTES = B + 2 * BN * 16;
 };
-
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ i32x16 mfma_i8(i32x4 a, i32x4 b, i32x16 c) {
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
-}
-
-// The 16 codes of one packed word as int8, element e in byte e % 4 of dword e / 4.
-__device__ __forceinline__ i32x4 decode_i8(uint32_t w) {
-    // bytes (magnitude even, magnitude odd, magnitude even, magnitude odd) and the same
-    // for the sign planes; both sources are w, so the byte order of the pair is immaterial
-    const uint32_t pm = __builtin_amdgcn_perm(w, w, 0x02000200u);
-    const uint32_t ps = __builtin_amdgcn_perm(w, w, 0x03010301u);
-    // element 4d + b: its magnitude to bit 2d of byte b, its sign to bit 2d + 1
-    const uint32_t m = (pm & 0x0000FFFFu) | ((pm >> 1) & 0xFFFF0000u);
-    const uint32_t s = ((ps << 1) & 0x0000FFFFu) | (ps & 0xFFFF0000u);
-    const uint32_t z = (m & 0x55555555u) | (s & 0xAAAAAAAAu);
-    constexpr uint32_t LUT = 0xFEFF0201u;  // index magnitude + 2 sign -> 1, 2, -1, -2
-    i32x4 r;
-    r.x = (int)__builtin_amdgcn_perm(LUT, LUT, z & 0x03030303u);
-    r.y = (int)__builtin_amdgcn_perm(LUT, LUT, (z >> 2) & 0x03030303u);
-    r.z = (int)__builtin_amdgcn_perm(LUT, LUT, (z >> 4) & 0x03030303u);
-    r.w = (int)__builtin_amdgcn_perm(LUT, LUT, (z >> 6) & 0x03030303u);
-    return r;
-}
 
 // UNI: C % 128 == 0, so all 128 elements of a stage share one tap (r, s) and the tap
 // bookkeeping is wave-uniform.  Otherwise C % 16 == 0 and every lane tracks the tap of its
@@ -460,13 +435,8 @@ bool conv_i8_eligible(const ConvI8Args& a) {
 
 int conv_i8_tile(const ConvI8Args& a) {
     const int forced = knob(KNOB_I8_TILE);
-    if (forced >= 1 && forced <= 4) return forced;
-    const int64_t M = (int64_t)a.N * a.P * a.Q;
-    int cfg = a.K > 128 ? 1 : (a.K > 64 ? 2 : 3);
-    const int bm = 128, bn = cfg == 1 ? 256 : (cfg == 2 ? 128 : 64);
-    // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles
-    if (((M + bm - 1) / bm) * ((a.K + bn - 1) / bn) < 384 && a.K >= 128) cfg = 4;
-    return cfg;
+    if (forced >= 1 && forced <= 8) return forced;
+    return conv_code8_tile(a.N, a.P, a.Q, a.K, (int64_t)a.R * a.S * a.C);
 }
 
 hipError_t launch_conv_i8(const ConvI8Args& args, hipStream_t stream) {
@@ -474,7 +444,9 @@ hipError_t launch_conv_i8(const ConvI8Args& args, hipStream_t stream) {
     ConvI8Args a = args;
     a.div_q = make_fastdiv((uint32_t)a.Q);
     a.div_pq = make_fastdiv((uint32_t)a.P * (uint32_t)a.Q);
-    switch (conv_i8_tile(a)) {
+    const int tile = conv_i8_tile(a);
+    if (tile >= 5) return launch_conv_i8_small(a, tile, stream);
+    switch (tile) {
         case 2: return launch_i8_cfg<128, 128, 2, 2, 3>(a, stream);
         case 3: return launch_i8_cfg<128, 64, 2, 2, 3>(a, stream);
         case 4: return launch_i8_cfg<64, 128, 1, 4, 4>(a, stream);

@@ -255,9 +255,13 @@ struct ConvI8Args {
     uint32_t rep_lo, rep_hi;  // sum_{r < R} 2^(r*S)
 };
 bool conv_i8_eligible(const ConvI8Args& a);
-// Tile shape (1: 128 x 256, 2: 128 x 128, 3: 128 x 64, 4: 64 x 128); the int8 tile knob forces one.
+// Tile shape (1: 128 x 256, 2: 128 x 128, 3: 128 x 64, 4: 64 x 128, small-layer kernel with filters
+// per tile and waves 5: 32, 4, 6: 32, 8, 7: 32, 16, 8: 64, 8); the int8 tile knob forces one.
 int conv_i8_tile(const ConvI8Args& a);
 hipError_t launch_conv_i8(const ConvI8Args& a, hipStream_t stream);
+// The built-in choice for K filters of n elements, either format.
+int conv_code8_tile(int32_t N, int32_t P, int32_t Q, int32_t K, int64_t n);
+hipError_t launch_conv_i8_small(const ConvI8Args& a, int cfg, hipStream_t stream);
 // q = clamp(round-half-even(x * inv), -127, 127), NaN -> 0; x bf16 or fp32.
 hipError_t launch_quantize_act_i8(const void* x, int x_f32, int64_t count, float inv, int8_t* q,
                                   hipStream_t stream);
@@ -278,9 +282,10 @@ struct ConvFp8Args {
     uint32_t rep_lo, rep_hi;  // sum_{r < R} 2^(r*S)
 };
 bool conv_fp8_eligible(const ConvFp8Args& a);
-// Tile shape (1: 128 x 256, 2: 128 x 128, 3: 128 x 64, 4: 64 x 128); the fp8 tile knob forces one.
+// Tile shape as for int8; the fp8 tile knob forces one.
 int conv_fp8_tile(const ConvFp8Args& a);
 hipError_t launch_conv_fp8(const ConvFp8Args& a, hipStream_t stream);
+hipError_t launch_conv_fp8_small(const ConvFp8Args& a, int cfg, hipStream_t stream);
 // q = E4M3(fp32(x * inv)): nearest, ties to even, saturating at +-448, NaN -> 0; x bf16 or fp32.
 hipError_t launch_quantize_act_fp8(const void* x, int x_f32, int64_t count, float inv, uint8_t* q,
                                    hipStream_t stream);
