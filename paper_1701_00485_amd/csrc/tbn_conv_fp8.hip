@@ -343,27 +343,17 @@ __global__ __launch_bounds__(256, 2) void conv_fp8_kernel(const ConvFp8Args a) {
     }
 }
 
-// E4M3 code of one fp32 value: nearest, ties to even, |v| > 448 -> +-448, NaN -> 0, the
-// sign bit kept for -0 and values that round to zero.  Below 2^-6 the codes are the
-// subnormals, v / 2^-9 rounded to an integer 0..8 (8 is the smallest normal, 0x08); above,
-// code = 8 (e + 7) + m with m = (v / 2^e - 1) * 8 rounded to an integer 0..8 (8 carries into
-// the exponent field).  Every scaling here is by a power of two, so exact, and rintf rounds
-// half to even.
-__device__ __forceinline__ uint32_t fp8_code(float v) {
-    const uint32_t bits = __float_as_uint(v);
-    const uint32_t sign = (bits >> 24) & 0x80u;
-    const float av = fabsf(v);
-    uint32_t mag;
-    if (!(av <= 448.0f)) {
-        mag = av != av ? 0xFFFFFFFFu : 0x7Eu;  // NaN marked, overflow saturates
-    } else if (av < 0.015625f) {
-        mag = (uint32_t)rintf(av * 512.0f);
-    } else {
-        const int e = (int)((__float_as_uint(av) >> 23) & 0xFF) - 127;  // av normal in fp32 here
-        const float frac = __uint_as_float((__float_as_uint(av) & 0x007FFFFFu) | 0x3F800000u);  // av / 2^e
-        mag = (uint32_t)(8 * (e + 7)) + (uint32_t)rintf((frac - 1.0f) * 8.0f);
-    }
-    return mag == 0xFFFFFFFFu ? 0u : (sign | mag);
+// E4M3 codes of two fp32 values in the low (high) half of a word: nearest, ties to even (the
+// conversion instruction's rounding), |v| > 448 -> +-448, NaN -> 0, the sign bit kept for -0 and values
+// that round to zero.  The same codes from exponent and fraction in integer arithmetic took about 25
+// instructions a value and bound the kernel: 17.8 us on 25.7 M bf16 values against 12.3
+// with this (6.3 TB/s).
+__device__ __forceinline__ float fp8_range(float v) {
+    return v != v ? 0.0f : __builtin_amdgcn_fmed3f(v, -448.0f, 448.0f);
+}
+template <bool HI>
+__device__ __forceinline__ uint32_t fp8_codes2(float a, float b, uint32_t word) {
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(fp8_range(a), fp8_range(b), (int)word, HI);
 }
 
 // codes of 16 activations per thread (v = x * inv in fp32 first)
@@ -403,7 +393,10 @@ __global__ __launch_bounds__(256) void quantize_act_fp8_kernel(const void* __res
     }
     uint32_t word[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int e = 0; e < 16; ++e) word[e / 4] |= fp8_code(v[e] * inv) << (8 * (e % 4));
+    for (int e = 0; e < 4; ++e) {
+        word[e] = fp8_codes2<false>(v[4 * e] * inv, v[4 * e + 1] * inv, 0u);
+        word[e] = fp8_codes2<true>(v[4 * e + 2] * inv, v[4 * e + 3] * inv, word[e]);
+    }
     if (full) {
         *reinterpret_cast<u32x4*>(q + i0) = u32x4{word[0], word[1], word[2], word[3]};
     } else {

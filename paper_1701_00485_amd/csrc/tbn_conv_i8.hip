@@ -387,13 +387,19 @@ __global__ __launch_bounds__(256) void quantize_act_i8_kernel(const void* __rest
             v[e] = F32 ? reinterpret_cast<const float*>(x)[i] : bf16_bits_to_f32(reinterpret_cast<const uint16_t*>(x)[i]);
         }
     }
-    uint32_t word[4] = {0u, 0u, 0u, 0u};
+    // limited to the range first (its bounds are integers, so that rounds to the same), then rounded
+    // half to even by adding 1.5 * 2^23: the integer is in the low byte, two's complement
+    uint32_t word[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const float t = v[e] * inv;
-        const float r = fminf(fmaxf(rintf(t), -127.0f), 127.0f);
-        const int c = t != t ? 0 : (int)r;
-        word[e / 4] |= ((uint32_t)c & 0xFFu) << (8 * (e % 4));
+    for (int d = 0; d < 4; ++d) {
+        uint32_t b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float t = v[4 * d + e] * inv;
+            b[e] = __float_as_uint((t != t ? 0.0f : __builtin_amdgcn_fmed3f(t, -127.0f, 127.0f)) + 12582912.0f);
+        }
+        const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x0C0C0400u);  // bytes 0 of b0, b1
+        word[d] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0C0C0400u), lo, 0x05040100u);
     }
     if (full) {
         *reinterpret_cast<u32x4*>(q + i0) = u32x4{word[0], word[1], word[2], word[3]};
@@ -447,7 +453,9 @@ hipError_t launch_conv_i8(const ConvI8Args& args, hipStream_t stream) {
     const int tile = conv_i8_tile(a);
     if (tile >= 5) return launch_conv_i8_small(a, tile, stream);
     switch (tile) {
-        case 2: return launch_i8_cfg<128, 128, 2, 2, 3>(a, stream);
+        // a wave per 32 filters, so that each decodes only its own (four MFMAs per decode instead of
+        // two): 28 x 28 x 128 -> 128 at batch 64 17.6 -> 15.8 us
+        case 2: return launch_i8_cfg<128, 128, 1, 4, 3>(a, stream);
         case 3: return launch_i8_cfg<128, 64, 2, 2, 3>(a, stream);
         case 4: return launch_i8_cfg<64, 128, 1, 4, 4>(a, stream);
         default: return launch_i8_cfg<128, 256, 1, 4, 3>(a, stream);

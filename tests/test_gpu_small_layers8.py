@@ -2,14 +2,17 @@
 oracle's bit for bit) and fp8 (within the bound derived from the matrix core's window), on layers at the
 edges of its tiles: one row, 31 to 33 rows, filter counts around 32 and 64 and no multiple of 4, fewer
 stages than waves and many more, odd numbers of 64-element code chunks, taps on every border, strides.
+And the E4M3 codes of fp32 values over all exponents, the halfway cases among them.
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import synth
 import test_gpu_fp8 as fp8
 import test_gpu_i8 as i8
-from test_gpu_parity import log
+from test_gpu_parity import log, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +36,16 @@ def test_small_layers_8bit(tbn, tile, knobs):
             ref = oracle.conv_fwd_fp8(d, xq, codes, alpha, x_scale, relu=relu)
             got = fp8._run(tbn, g, xq, words, alpha, x_scale, out, relu)
             fp8.check(got, ref.reshape(got.shape), d, xq, alpha, x_scale, out)
+
+
+def test_fp8_codes_of_fp32_values(tbn):
+    g = synth.rng(9, "fp8 fp32 values")
+    bits = g.integers(0, 1 << 32, size=1 << 18, dtype=np.uint64).astype(np.uint32)  # every exponent, NaN, inf
+    near = (g.integers(0, 1 << 24, size=1 << 18) / np.float64(1 << 15)).astype(np.float32)  # 0 .. 512 in 2^-15
+    half = np.concatenate([np.arange(0, 1 << 12) * np.float32(2.0 ** -11), np.arange(0, 1 << 10) * np.float32(0.5)])
+    x = np.concatenate([bits.view(np.float32), near, -near, half.astype(np.float32), -half.astype(np.float32)])
+    for inv in (np.float32(1.0), np.float32(0.37)):
+        log("fp8 codes of %d fp32 values, inverse scale %g" % (x.size, inv))
+        got = tbn.quantize_act_fp8(to_dev(x), float(inv))
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), oracle.quantize_act_fp8(x, inv))
