@@ -315,9 +315,11 @@ hipError_t launch_maxpool_bwd(const PoolArgs& a, const uint16_t* dy, const int32
 hipError_t launch_avgpool(int32_t N, int32_t HW, int32_t C, const uint16_t* x, void* y, int y_f32, hipStream_t s);
 // Batch normalisation statistics: per-chunk partial sums in workspace, then per channel.
 struct BnPlan {
-    int64_t rpc, chunks;  // rows per chunk, chunks
+    int64_t rpc, chunks;  // rows per chunk (of 8 rows each where kind says so), chunks
+    int64_t blocks;       // of the element-wise passes
     int32_t slices;       // groups of 256 channel groups
-    int32_t vec;          // C % 8 == 0: 8 channels per 16-byte access
+    int32_t tpr;          // rows a block covers at a time
+    int32_t kind;         // 8 channels per thread, 8 values over uneven channels, or one channel
     size_t ws_bytes;      // two fp32 partial arrays [chunks][C]
 };
 BnPlan plan_bn(int64_t rows, int32_t C);
