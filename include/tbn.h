@@ -179,6 +179,18 @@ tbn_status tbn_conv2d_fwd_noalloc(const tbn_conv_desc* desc, const void* x, tbn_
                                   hipStream_t stream);
 
 /*
+ * An image stem in one pass: y = 3x3 / 2 max pooling with border 1 of
+ * relu(alpha_k * scale_k * (x conv W~) + bias_k), bf16 NHWC [N][(P+1)/2][(Q+1)/2][K], the values of
+ * tbn_conv2d_fwd to bf16 followed by tbn_maxpool2d_fwd.  scale and bias are optional.  For layers of few
+ * channels (C < 8) with an input of a million elements or more and K % 8 == 0; TBN_ERR_UNSUPPORTED
+ * from both calls for any other (run the two separate passes).
+ */
+tbn_status tbn_conv2d_relu_maxpool_workspace_size(const tbn_conv_desc* desc, tbn_dtype xt, size_t* bytes);
+tbn_status tbn_conv2d_relu_maxpool_fwd(const tbn_conv_desc* desc, const void* x, tbn_dtype xt, const uint32_t* codes,
+                                       const float* alpha, const float* scale, const float* bias, void* y,
+                                       void* workspace, size_t workspace_bytes, hipStream_t stream);
+
+/*
  * Integer-activation variant of the forward pass (an extension of Sec. 2 Eq. 1: the paper
  * keeps activations in full precision; its Sec. 1 motivates the two-bit filters by
  * arithmetic without multipliers).  The input I is represented as s * q, q int8, and the

@@ -89,6 +89,8 @@ def load():
         "tbn_quantize": ([vp, i64, i64, vp, vp, vp, vp], i32),
         "tbn_quantize_variant": ([vp, i64, i64, f32, vp, vp, vp, vp, vp], i32),
         "tbn_conv2d_fwd": ([vp, vp, i32, vp, vp, vp, vp, i32, vp, ctypes.c_size_t, vp], i32),
+        "tbn_conv2d_relu_maxpool_workspace_size": ([vp, i32, vp], i32),
+        "tbn_conv2d_relu_maxpool_fwd": ([vp, vp, i32, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp], i32),
         "tbn_conv2d_fwd_dense": ([vp, vp, i32, vp, vp, vp, i32, vp], i32),
         "tbn_quantize_act_i8": ([vp, i32, i64, f32, vp, vp], i32),
         "tbn_conv2d_fwd_i8": ([vp, vp, vp, vp, f32, i32, vp, i32, vp], i32),
@@ -139,6 +141,7 @@ def exported_symbols():
     return sorted(["tbn_status_str", "tbn_last_error", "tbn_conv_out_dims", "tbn_packed_words",
                    "tbn_packed_row_words", "tbn_packed_bytes",
                    "tbn_workspace_size", "tbn_quantize", "tbn_quantize_variant", "tbn_conv2d_fwd", "tbn_conv2d_fwd_dense",
+                   "tbn_conv2d_relu_maxpool_workspace_size", "tbn_conv2d_relu_maxpool_fwd",
                    "tbn_quantize_act_i8", "tbn_conv2d_fwd_i8",
                    "tbn_quantize_act_fp8", "tbn_repack_codes_fp4", "tbn_conv2d_fwd_fp8",
                    "tbn_conv2d_bwd_data",
@@ -356,6 +359,27 @@ def conv2d_fwd(desc: ConvDesc, x, codes, alpha, y=None, out_dtype=torch.bfloat16
           ctypes.byref(ep) if ep is not None else None, _dev(y, "y", (torch.bfloat16, torch.float32)),
           _dtype_code(y.dtype), _dev(ws, "ws") if ws is not None else None,
           ws.numel() * ws.element_size() if ws is not None else 0, _stream())
+    return y
+
+
+def conv2d_relu_maxpool_fwd(desc: ConvDesc, x, codes, alpha, scale=None, bias=None):
+    """3x3 / 2 max pooling (border 1) of relu(conv2d_fwd(...)) in one pass, bf16 NHWC; None where the
+    layer has no fused form (few channels, large input only: see tbn_conv2d_relu_maxpool_fwd)."""
+    need = ctypes.c_size_t()
+    xt = _dtype_code(x.dtype)
+    if load().tbn_conv2d_relu_maxpool_workspace_size(ctypes.byref(desc), xt, ctypes.byref(need)):
+        return None
+    P, Q = desc.out_dims()
+    _numel(x, desc.n * desc.h * desc.w * desc.c, "x")
+    _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
+    _numel(alpha, desc.k, "alpha")
+    y = torch.empty((desc.n, (P + 1) // 2, (Q + 1) // 2, desc.k), dtype=torch.bfloat16, device=x.device)
+    ws = torch.empty(need.value, dtype=torch.uint8, device=x.device)
+    _call("tbn_conv2d_relu_maxpool_fwd", ctypes.byref(desc), _dev(x, "x", (torch.bfloat16, torch.float32)), xt,
+          _dev(codes, "codes", (torch.int32,)), _dev(alpha, "alpha", (torch.float32,)),
+          _dev(scale, "scale", (torch.float32,)) if scale is not None else None,
+          _dev(bias, "bias", (torch.float32,)) if bias is not None else None, _dev(y, "y"), _dev(ws, "ws"),
+          need.value, _stream())
     return y
 
 

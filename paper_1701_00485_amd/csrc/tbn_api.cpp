@@ -351,6 +351,47 @@ tbn_status tbn_conv2d_fwd(const tbn_conv_desc* desc, const void* x, tbn_dtype xt
     return e == hipSuccess ? TBN_OK : hip_fail(e, "tbn_conv2d_fwd");
 }
 
+tbn_status tbn_conv2d_relu_maxpool_workspace_size(const tbn_conv_desc* desc, tbn_dtype xt, size_t* bytes) {
+    Geometry g;
+    tbn_status st = check_desc(desc, &g);
+    if (st != TBN_OK) return st;
+    if (!bytes) return fail(TBN_ERR_NULL, "bytes is required");
+    if (xt != TBN_BF16 && xt != TBN_F32) return fail(TBN_ERR_UNSUPPORTED, "unknown dtype");
+    tbn::ThinGeom tg;
+    if (!tbn::conv_pool_plan(fwd_args(g, xt, TBN_BF16), &tg))
+        return fail(TBN_ERR_UNSUPPORTED, "no fused form of this layer");
+    *bytes = (size_t)tg.ws_bytes;
+    return TBN_OK;
+}
+
+tbn_status tbn_conv2d_relu_maxpool_fwd(const tbn_conv_desc* desc, const void* x, tbn_dtype xt, const uint32_t* codes,
+                                       const float* alpha, const float* scale, const float* bias, void* y, void* ws,
+                                       size_t ws_bytes, hipStream_t stream) {
+    Geometry g;
+    tbn_status st = check_desc(desc, &g);
+    if (st != TBN_OK) return st;
+    if (!x || !codes || !alpha || !y) return fail(TBN_ERR_NULL, "x, codes, alpha and y are required");
+    if (xt != TBN_BF16 && xt != TBN_F32) return fail(TBN_ERR_UNSUPPORTED, "unknown dtype");
+    if (!aligned16(x) || !aligned16(codes) || !aligned16(y) || !aligned4(alpha) || (scale && !aligned4(scale)) ||
+        (bias && !aligned4(bias)))
+        return fail(TBN_ERR_ALIGN, "x, codes and y must be 16-byte aligned");
+    tbn::ConvGemmArgs a = fwd_args(g, xt, TBN_BF16);
+    tbn::ThinGeom tg;
+    if (!tbn::conv_pool_plan(a, &tg)) return fail(TBN_ERR_UNSUPPORTED, "no fused form of this layer");
+    if (!ws || ws_bytes < (size_t)tg.ws_bytes) return fail(TBN_ERR_WORKSPACE, "workspace too small");
+    if (!aligned16(ws)) return fail(TBN_ERR_ALIGN, "workspace must be 16-byte aligned");
+    a.partial = reinterpret_cast<float*>(ws);
+    a.x = x;
+    a.codes = codes;
+    a.colscale = alpha;
+    a.scale = scale;
+    a.bias = bias;
+    a.relu = 1;
+    a.y = y;
+    const hipError_t e = tbn::launch_conv_thin_pool(a, tg, stream);
+    return e == hipSuccess ? TBN_OK : hip_fail(e, "tbn_conv2d_relu_maxpool_fwd");
+}
+
 tbn_status tbn_conv2d_fwd_dense(const tbn_conv_desc* desc, const void* x, tbn_dtype xt, const float* w,
                                 const tbn_epilogue* ep, void* y, tbn_dtype yt, hipStream_t stream) {
     Geometry g;

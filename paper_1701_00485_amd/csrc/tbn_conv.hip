@@ -349,6 +349,11 @@ size_t conv_gemm_partial_bytes(const ConvGemmArgs& a) {
     }
 }
 
+bool conv_pool_plan(const ConvGemmArgs& a, ThinGeom* g) {
+    FcStreamPlan fp;
+    return choose_path(a, conv_tile_override(), &fp, g) == PATH_THIN && conv_thin_pool_plan(a, g);
+}
+
 static ConvGemmArgs padded_args(const ConvGemmArgs& a, int32_t Cp) {
     ConvGemmArgs b = a;
     b.C = Cp;

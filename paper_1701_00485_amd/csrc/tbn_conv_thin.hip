@@ -82,16 +82,18 @@ __device__ __forceinline__ uint32_t load_patch(const ConvGemmArgs& a, const uint
 }
 
 // The zero-bordered copy of the input: xp[n][h'][w'][c] = x[n][h' - ph][w' - pw][c] inside
-// the image and for c < C, else 0 (bf16).  One thread per padded pixel, CP elements each.
+// the image and for c < C, else 0 (bf16).  One thread per padded pixel, CP elements each; pixel
+// indices below 2^32 (the copy is below 2 GiB), split by multiply-shift divisions: 15.1 us with 64-bit
+// divisions, 12.2 us without (64 x 224 x 224 x 3).
 template <int CP, bool X32>
 __global__ __launch_bounds__(256) void thin_pad_kernel(const ConvGemmArgs a, const ThinGeom g, uint16_t* xp) {
-    const int64_t total = (int64_t)a.N * g.Hp * g.Wp;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t total = (uint32_t)a.N * (uint32_t)g.Hp * (uint32_t)g.Wp;
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i >= total) return;
-    const int64_t hw = (int64_t)g.Hp * g.Wp;
-    const int n = (int)(i / hw);
-    const int rem = (int)(i - (int64_t)n * hw);
-    const int hp = rem / g.Wp, wp = rem - (rem / g.Wp) * g.Wp;
+    const uint32_t row = fdiv(i, g.div_wp);
+    const int wp = (int)(i - row * (uint32_t)g.Wp);
+    const uint32_t n = fdiv(row, g.div_hp);
+    const int hp = (int)(row - n * (uint32_t)g.Hp);
     const int h = hp - a.ph, w = wp - a.pw;
     const bool in = (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W;
     const int64_t src = (((int64_t)n * a.H + h) * a.W + w) * a.C;
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(256) void thin_pad_kernel(const ConvGemmArgs a, con
                     : reinterpret_cast<const uint16_t*>(a.x)[src + c];
         v[c] = e;
     }
-    uint16_t* dst = xp + i * CP;
+    uint16_t* dst = xp + (int64_t)i * CP;
     if constexpr (CP == 1) {
         dst[0] = (uint16_t)v[0];
     } else if constexpr (CP == 2) {
@@ -114,6 +116,121 @@ __global__ __launch_bounds__(256) void thin_pad_kernel(const ConvGemmArgs a, con
     } else {
         *reinterpret_cast<u32x4*>(dst) =
             u32x4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+    }
+}
+
+// The block's filters into LDS as bf16, zero at padding taps / channels / filters: the packed codes
+// (NB KiB, contiguous in the blocked layout, staged in cw) decoded to W~, or the real filters of a
+// full-precision layer rounded to bf16.  The caller's barrier completes it.
+template <int CP>
+__device__ __forceinline__ void decode_filters(const ConvGemmArgs& a, const ThinGeom& g, uint16_t* wl, uint32_t* cw) {
+    const int tid = threadIdx.x;
+    const int K = a.Kf, C = a.C, S = a.S;
+    const int n = a.R * S * C;
+    const int NB = (n + 63) / 64;
+    const int k0 = blockIdx.y * FB;
+    if (a.wdense) {
+        // a full-precision layer: its real filters rounded to bf16 (nearest even)
+        const int f = tid >> 2;
+        const bool fk = k0 + f < K;
+        for (int j = tid & 3; j < g.WPITCH; j += 4) {
+            uint32_t v = 0;
+            if (j < g.RT && fk) {
+                const int r = j >> g.logT, t = j & (g.T - 1);
+                const int s = t / CP, c = t & (CP - 1);
+                if (s < S && c < C) v = f32_to_bf16_bits(a.wdense[(int64_t)(k0 + f) * n + (r * S + s) * C + c]);
+            }
+            wl[f * g.WPITCH + j] = (uint16_t)v;
+        }
+    } else {
+        {
+            const u32x4* src = reinterpret_cast<const u32x4*>(a.codes + (int64_t)blockIdx.y * NB * 256);
+            for (int i = tid; i < NB * 64; i += 256) reinterpret_cast<u32x4*>(cw)[i] = src[i];
+        }
+        __syncthreads();
+        const int f = tid >> 2;  // 4 threads per filter row
+        const bool fk = k0 + f < K;
+        for (int j = tid & 3; j < g.WPITCH; j += 4) {
+            uint32_t v = 0;
+            if (j < g.RT && fk) {
+                const int r = j >> g.logT, t = j & (g.T - 1);
+                const int s = t / CP, c = t & (CP - 1);
+                if (s < S && c < C) {
+                    const int i = (r * S + s) * C + c;
+                    const uint32_t w = cw[((i >> 6) * 64 + f) * 4 + ((i & 63) >> 4)];
+                    const int jj = (i & 15) >> 1, hh = i & 1;
+                    const uint32_t mag = (w >> (16 * hh + jj)) & 1u, sg = (w >> (16 * hh + 8 + jj)) & 1u;
+                    v = 0x3F80u + (mag << 7) + (sg << 15);  // bf16 of +-1 / +-2
+                }
+            }
+            wl[f * g.WPITCH + j] = (uint16_t)v;
+        }
+    }
+}
+
+// Two output rows of 32 pixels against the 64 filters: abase is this lane's pixel of the first row in
+// the patch, arow2 the patch offset of the second, arowr that of filter row r + 1.
+template <int CP, int TT>
+__device__ __forceinline__ void two_rows_mfma(const uint16_t* abase, int arow2, int arowr, const uint16_t* bbase,
+                                              int wpitch, int R, f32x16 (&acc)[2][2]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[u][t][v] = 0.0f;
+    // flat reduction steps j = r * TT + t (16 elements each); the filters are contiguous
+    // in j, the patch advances a row every TT steps.  Two operand sets alternate, the
+    // reads of step j + 1 issued before the MFMAs of step j (no copies at the loop edge)
+    const int J = R * TT;
+    bf16x8 xa[2], xb[2], wa[2], wb[2];
+    auto rd = [&](int j, int s) {
+        const uint16_t* an = abase + (j / TT) * arowr + 16 * (j % TT);
+        xa[s] = load8<CP>(an);
+        xb[s] = load8<CP>(an + arow2);
+        wa[s] = *reinterpret_cast<const bf16x8*>(bbase + 16 * j);
+        wb[s] = *reinterpret_cast<const bf16x8*>(bbase + 32 * wpitch + 16 * j);
+    };
+    auto mm = [&](int s) {
+        acc[0][0] = mfma32(wa[s], xa[s], acc[0][0]);
+        acc[0][1] = mfma32(wb[s], xa[s], acc[0][1]);
+        acc[1][0] = mfma32(wa[s], xb[s], acc[1][0]);
+        acc[1][1] = mfma32(wb[s], xb[s], acc[1][1]);
+    };
+    rd(0, 0);
+    int j = 0;
+    for (; j + 2 <= J; j += 2) {
+        rd(j + 1, 1);
+        mm(0);
+        if (j + 2 < J) rd(j + 2, 0);
+        mm(1);
+    }
+    if (j < J) mm(0);  // odd step count: the last step's operands are in set 0
+}
+
+// The byte offsets, relative to a patch's origin in the zero-bordered copy, of the pieces this lane
+// copies: piece k = 64 (4 i + wave) + lane of the patch is row k / ppr, 16-byte column k % ppr, and
+// lands at LDS byte 16 k of the patch buffer (pieces past the patch get an out-of-range offset and land
+// as zeros in the buffer's tail).
+constexpr int kMaxNi = 8;
+template <int CP>
+__device__ __forceinline__ void patch_offsets(const ThinGeom& g, int wave, int lane, uint32_t (&prel)[kMaxNi]) {
+#pragma unroll
+    for (int i = 0; i < kMaxNi; ++i) {
+        const int k = 64 * (4 * i + wave) + lane;
+        const int r = k / g.ppr, j = k - (k / g.ppr) * g.ppr;
+        prel[i] = (i < g.ni && k < g.npieces) ? (uint32_t)((r * g.Wp * CP + 8 * j) * 2) : 0x80000000u;
+    }
+}
+
+__device__ __forceinline__ void copy_patch(const ThinGeom& g, v4i rs_xp, const uint32_t (&prel)[kMaxNi], uint32_t toff,
+                                           int wave, uint16_t* buf) {
+    const uint32_t base = lds_addr(buf);
+#pragma unroll
+    for (int i = 0; i < kMaxNi; ++i) {
+        if (i < g.ni)
+            dma_b128(rs_xp, base + (uint32_t)(64 * (4 * i + wave)) * 16u,
+                     prel[i] >= 0x80000000u ? 0x80000000u : prel[i] + toff);
     }
 }
 
@@ -132,9 +249,7 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(const ConvGemmArgs a, co
     const int l32 = lane & 31;
     float* st = reinterpret_cast<float*>(lds + g.s_off) + wave * 32 * SPITCH;
 
-    const int K = a.Kf, C = a.C, R = a.R, S = a.S;
-    const int n = R * S * C;
-    const int NB = (n + 63) / 64;
+    const int K = a.Kf, C = a.C, R = a.R;
     const int k0 = blockIdx.y * FB;
 
     // tile index -> (image, first output row, first output column), by multiply-shift
@@ -176,47 +291,7 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(const ConvGemmArgs a, co
         }
     }
 
-    // ---- the block's filters into LDS as bf16, zero at padding taps / channels / filters:
-    //      the packed codes (NB KiB, contiguous in the blocked layout) decoded to W~, or
-    //      the real filters of a full-precision layer rounded to bf16 ----
-    uint32_t* cw = reinterpret_cast<uint32_t*>(lds + g.s_off);
-    if (a.wdense) {
-        // a full-precision layer: its real filters rounded to bf16 (nearest even)
-        const int f = tid >> 2;
-        const bool fk = k0 + f < K;
-        for (int j = tid & 3; j < g.WPITCH; j += 4) {
-            uint32_t v = 0;
-            if (j < g.RT && fk) {
-                const int r = j >> g.logT, t = j & (g.T - 1);
-                const int s = t / CP, c = t & (CP - 1);
-                if (s < S && c < C) v = f32_to_bf16_bits(a.wdense[(int64_t)(k0 + f) * n + (r * S + s) * C + c]);
-            }
-            wl[f * g.WPITCH + j] = (uint16_t)v;
-        }
-    } else {
-        {
-            const u32x4* src = reinterpret_cast<const u32x4*>(a.codes + (int64_t)blockIdx.y * NB * 256);
-            for (int i = tid; i < NB * 64; i += 256) reinterpret_cast<u32x4*>(cw)[i] = src[i];
-        }
-        __syncthreads();
-        const int f = tid >> 2;  // 4 threads per filter row
-        const bool fk = k0 + f < K;
-        for (int j = tid & 3; j < g.WPITCH; j += 4) {
-            uint32_t v = 0;
-            if (j < g.RT && fk) {
-                const int r = j >> g.logT, t = j & (g.T - 1);
-                const int s = t / CP, c = t & (CP - 1);
-                if (s < S && c < C) {
-                    const int i = (r * S + s) * C + c;
-                    const uint32_t w = cw[((i >> 6) * 64 + f) * 4 + ((i & 63) >> 4)];
-                    const int jj = (i & 15) >> 1, hh = i & 1;
-                    const uint32_t mag = (w >> (16 * hh + jj)) & 1u, sg = (w >> (16 * hh + 8 + jj)) & 1u;
-                    v = 0x3F80u + (mag << 7) + (sg << 15);  // bf16 of +-1 / +-2
-                }
-            }
-            wl[f * g.WPITCH + j] = (uint16_t)v;
-        }
-    }
+    decode_filters<CP>(a, g, wl, reinterpret_cast<uint32_t*>(lds + g.s_off));
 
     // ---- epilogue constants: this lane always writes channels k0 + 32 t + 8 (lane % 4) + 0..7 ----
     float cs[2][8], bi[2][8];
@@ -251,45 +326,10 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(const ConvGemmArgs a, co
             }
         }
     };
-    // the tile's reduction: wave w computes output rows w and w + 4 of the tile
+    // wave w computes output rows w and w + 4 of the tile
     auto tile_mfma = [&](const uint16_t* cur, f32x16 (&acc)[2][2]) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[u][t][v] = 0.0f;
-        const uint16_t* abase = cur + ((wave * a.sh) * g.PW + l32 * a.sw) * CP + 8 * half;
-        const int arow4 = 4 * a.sh * g.PW * CP;  // patch offset of output row + 4
-        const int arowr = g.PW * CP;             // patch offset of filter row r + 1
-        const uint16_t* bbase = wl + l32 * g.WPITCH + 8 * half;
-        // flat reduction steps j = r * TT + t (16 elements each); the filters are contiguous
-        // in j, the patch advances a row every TT steps.  Two operand sets alternate, the
-        // reads of step j + 1 issued before the MFMAs of step j (no copies at the loop edge)
-        const int J = R * TT;
-        bf16x8 xa[2], xb[2], wa[2], wb[2];
-        auto rd = [&](int j, int s) {
-            const uint16_t* an = abase + (j / TT) * arowr + 16 * (j % TT);
-            xa[s] = load8<CP>(an);
-            xb[s] = load8<CP>(an + arow4);
-            wa[s] = *reinterpret_cast<const bf16x8*>(bbase + 16 * j);
-            wb[s] = *reinterpret_cast<const bf16x8*>(bbase + 32 * g.WPITCH + 16 * j);
-        };
-        auto mm = [&](int s) {
-            acc[0][0] = mfma32(wa[s], xa[s], acc[0][0]);
-            acc[0][1] = mfma32(wb[s], xa[s], acc[0][1]);
-            acc[1][0] = mfma32(wa[s], xb[s], acc[1][0]);
-            acc[1][1] = mfma32(wb[s], xb[s], acc[1][1]);
-        };
-        rd(0, 0);
-        int j = 0;
-        for (; j + 2 <= J; j += 2) {
-            rd(j + 1, 1);
-            mm(0);
-            if (j + 2 < J) rd(j + 2, 0);
-            mm(1);
-        }
-        if (j < J) mm(0);  // odd step count: the last step's operands are in set 0
+        two_rows_mfma<CP, TT>(cur + ((wave * a.sh) * g.PW + l32 * a.sw) * CP + 8 * half, 4 * a.sh * g.PW * CP,
+                              g.PW * CP, wl + l32 * g.WPITCH + 8 * half, g.WPITCH, R, acc);
     };
 
     auto tile_epilogue = [&](const f32x16 (&acc)[2][2], int64_t cimg, int cp0, int cq0) {
@@ -348,31 +388,15 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(const ConvGemmArgs a, co
     };
 
     if constexpr (DMA) {
-        // byte offsets, relative to the patch origin in the zero-bordered copy, of the pieces
-        // this lane copies: piece k = 64 (4 i + wave) + lane of the patch is row k / ppr,
-        // 16-byte column k % ppr, and lands at LDS byte 16 k of the patch buffer (pieces past
-        // the patch get an out-of-range offset and land as zeros in the buffer's tail)
-        constexpr int kMaxNi = 8;
         uint32_t prel[kMaxNi];
-#pragma unroll
-        for (int i = 0; i < kMaxNi; ++i) {
-            const int k = 64 * (4 * i + wave) + lane;
-            const int r = k / g.ppr, j = k - (k / g.ppr) * g.ppr;
-            prel[i] = (i < g.ni && k < g.npieces) ? (uint32_t)((r * g.Wp * CP + 8 * j) * 2) : 0x80000000u;
-        }
+        patch_offsets<CP>(g, wave, lane, prel);
         const v4i rs_xp = make_rsrc(a.partial, (uint32_t)g.ws_bytes);
         auto issue_patch = [&](int64_t t, uint16_t* buf) {
             int64_t im;
             int tp0, tq0;
             origin(t, &im, &tp0, &tq0);
             const uint32_t toff = (uint32_t)((((int64_t)im * g.Hp + (int64_t)tp0 * a.sh) * g.Wp + (int64_t)tq0 * a.sw) * CP * 2);
-            const uint32_t base = lds_addr(buf);
-#pragma unroll
-            for (int i = 0; i < kMaxNi; ++i) {
-                if (i < g.ni)
-                    dma_b128(rs_xp, base + (uint32_t)(64 * (4 * i + wave)) * 16u,
-                             prel[i] >= 0x80000000u ? 0x80000000u : prel[i] + toff);
-            }
+            copy_patch(g, rs_xp, prel, toff, wave, buf);
         };
         int64_t tile = blockIdx.x;
         if (tile < g.ntiles) issue_patch(tile, pl);
@@ -424,6 +448,177 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(const ConvGemmArgs a, co
     }
 }
 
+// Convolution, ReLU and 3x3 / 2 max pooling (border 1) in one pass, so that the convolution's output --
+// four times the pooled one -- never goes to memory.  A tile is 8 output rows x 32 output columns from
+// column 30 tq - 1 on: 4 x 15 pooled outputs (rows 4 i .. 4 i + 3 of tile row i, columns 15 tq ..
+// 15 tq + 14) and, with the row above the tile, everything that they cover.  Wave w computes rows 2 w
+// and 2 w + 1, takes the maximum over three neighbouring columns of each with lane shifts, and over
+// rows 2 w - 1 .. 2 w + 1, the first of them from the wave (or, for wave 0, the tile) above through LDS.
+// A block walks down a segment of a column of tiles (g.seg of them); the row above a segment that does
+// not begin at the top is computed first, by the tile above's last wave alone.  After ReLU every value is
+// +0 or above (a maximum of NaN and 0 is 0), so bf16 bits order as whole numbers and rows and columns
+// outside the output count as 0.  What bounds it: the reduction's LDS reads (two 16-byte reads per
+// MFMA) beside the copies; 48.5 us at 64 x 224 x 224 x 3, 7x7 / 2 to 64 filters, where the convolution
+// takes 53 us and the pooling 28 us (they read and write 103 MB between them).
+using u16x2 = __attribute__((ext_vector_type(2))) uint16_t;
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t p, uint32_t q) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, p),
+                                                                  __builtin_bit_cast(u16x2, q)));
+}
+
+template <int CP, int TT>
+__global__ __launch_bounds__(256) void conv_thin_pool_kernel(const ConvGemmArgs a, const ThinGeom g) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    uint16_t* wl = reinterpret_cast<uint16_t*>(lds + g.w_off);  // [FB][WPITCH]
+    uint16_t* pl = reinterpret_cast<uint16_t*>(lds + g.p_off);  // two patches [PH][PW][CP]
+    u32x4* rows = reinterpret_cast<u32x4*>(lds + g.s_off);      // [2 tiles][4 waves][4][32 odd columns]
+    float* fac = reinterpret_cast<float*>(lds + g.s_off + 16384);  // factor [64], bias [64]
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int half = lane >> 5;
+    const int l32 = lane & 31;
+    const int K = a.Kf;
+    const int k0 = blockIdx.y * FB;
+    const uint32_t PP = ((uint32_t)a.P + 1) / 2, PQ = ((uint32_t)a.Q + 1) / 2;
+
+    decode_filters<CP>(a, g, wl, reinterpret_cast<uint32_t*>(rows));
+    if (tid < FB) {
+        const int col = k0 + tid;
+        const bool ok = col < K;
+        float sc = ok ? a.colscale[col] : 0.0f;
+        if (ok && a.scale) sc *= a.scale[col];
+        fac[tid] = sc;
+        fac[FB + tid] = ok && a.bias ? a.bias[col] : 0.0f;
+    }
+    __syncthreads();
+
+    uint32_t prel[kMaxNi];
+    patch_offsets<CP>(g, wave, lane, prel);
+    const v4i rs_xp = make_rsrc(a.partial, (uint32_t)g.ws_bytes);
+    // item -> (image, tile column, segment); a step is tile row i of an item
+    struct Step {
+        int64_t item;
+        uint32_t img;
+        int tq, i, beg, end;  // i = beg - 1: the row above the segment
+    };
+    auto start = [&](int64_t item, Step* s) {
+        s->item = item;
+        const uint32_t im = fdiv((uint32_t)item, g.div_pqt);
+        const uint32_t rem = (uint32_t)item - im * (uint32_t)(g.tiles_q * g.segs);
+        const uint32_t sg = fdiv(rem, g.div_tq);
+        s->img = im;
+        s->tq = (int)(rem - sg * (uint32_t)g.tiles_q);
+        s->beg = (int)sg * g.seg;
+        s->end = min(g.tiles_p, s->beg + g.seg);
+        s->i = s->beg > 0 ? s->beg - 1 : 0;
+    };
+    auto next = [&](const Step& c, Step* s) {
+        *s = c;
+        if (c.i + 1 < c.end) {
+            ++s->i;
+        } else {
+            start(c.item + gridDim.x, s);
+        }
+    };
+    auto issue = [&](const Step& s, uint16_t* buf) {
+        const uint32_t toff = (uint32_t)(
+            (((int64_t)s.img * g.Hp + (int64_t)s.i * TP * a.sh) * g.Wp + (int64_t)s.tq * (TQ - 2) * a.sw) * CP * 2);
+        copy_patch(g, rs_xp, prel, toff, wave, buf);
+    };
+
+    Step cur, nxt;
+    start(blockIdx.x, &cur);
+    if (cur.item < g.ntiles) issue(cur, pl);
+    wait_vmcnt(0);
+    __syncthreads();
+    for (int it = 0; cur.item < g.ntiles; cur = nxt, it ^= 1) {
+        next(cur, &nxt);
+        // the next patch goes to the buffer that every wave finished reading before the last barrier
+        if (nxt.item < g.ntiles) issue(nxt, pl + (it ^ 1) * g.pbuf);
+        const bool above = cur.i < cur.beg;  // only the tile's last row is wanted
+        uint32_t v0[16], v1[16];             // rows 2 w and 2 w + 1: [t][group of 8 filters][pair]
+        if (!above || wave == 3) {
+            f32x16 acc[2][2];
+            two_rows_mfma<CP, TT>(
+                pl + it * g.pbuf + ((2 * wave * a.sh) * g.PW + l32 * a.sw) * CP + 8 * half, a.sh * g.PW * CP,
+                g.PW * CP, wl + l32 * g.WPITCH + 8 * half, g.WPITCH, a.R, acc);
+            const int q = cur.tq * (TQ - 2) - 1 + l32;
+            const int p = cur.i * TP + 2 * wave;
+            const bool okq = (unsigned)q < (unsigned)a.Q;
+            const bool ok0 = okq && p < a.P, ok1 = okq && p + 1 < a.P;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    const int f = 32 * t + 8 * gq + 4 * half;
+                    const f32x4 cs = *reinterpret_cast<const f32x4*>(fac + f);
+                    const f32x4 bi = *reinterpret_cast<const f32x4*>(fac + FB + f);
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int r = 4 * gq + 2 * e;
+                        const uint32_t w0 =
+                            pack_bf16x2(fmaxf(acc[0][t][r] * cs[2 * e] + bi[2 * e], 0.0f),
+                                        fmaxf(acc[0][t][r + 1] * cs[2 * e + 1] + bi[2 * e + 1], 0.0f));
+                        const uint32_t w1 =
+                            pack_bf16x2(fmaxf(acc[1][t][r] * cs[2 * e] + bi[2 * e], 0.0f),
+                                        fmaxf(acc[1][t][r + 1] * cs[2 * e + 1] + bi[2 * e + 1], 0.0f));
+                        v0[8 * t + 2 * gq + e] = ok0 ? w0 : 0u;
+                        v1[8 * t + 2 * gq + e] = ok1 ? w1 : 0u;
+                    }
+                }
+            // three neighbouring columns (used at odd lanes 1..29 only, whose neighbours are in their half)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                v0[j] = max_u16x2(v0[j], v1[j]);
+                const uint32_t l0 = __builtin_amdgcn_update_dpp(0u, v0[j], 0x138, 0xF, 0xF, true);
+                const uint32_t r0 = __builtin_amdgcn_update_dpp(0u, v0[j], 0x130, 0xF, 0xF, true);
+                const uint32_t l1 = __builtin_amdgcn_update_dpp(0u, v1[j], 0x138, 0xF, 0xF, true);
+                const uint32_t r1 = __builtin_amdgcn_update_dpp(0u, v1[j], 0x130, 0xF, 0xF, true);
+                v0[j] = max_u16x2(v0[j], max_u16x2(l0, r0));
+                v1[j] = max_u16x2(v1[j], max_u16x2(l1, r1));
+            }
+        }
+        // the odd rows through LDS; the slot of the row above the tile was written in the step before
+        // (a wave writes the same slot again two steps on, behind the barrier that follows these reads)
+        u32x4 up[4];
+        const int slot = 16 * half + (l32 >> 1);
+        if (wave == 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                up[j] = cur.i > 0 ? rows[(((it ^ 1) * 4 + 3) * 4 + j) * 32 + slot] : u32x4{0u, 0u, 0u, 0u};
+        }
+        if ((l32 & 1) && (!above || wave == 3)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                rows[((it * 4 + wave) * 4 + j) * 32 + slot] =
+                    u32x4{v1[4 * j], v1[4 * j + 1], v1[4 * j + 2], v1[4 * j + 3]};
+        }
+        wait_vmcnt(0);    // this wave's pieces of the next patch have landed
+        __syncthreads();  // ... and every wave's; the odd rows are in place
+        if (above) continue;
+        if (wave != 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) up[j] = rows[((it * 4 + wave - 1) * 4 + j) * 32 + slot];
+        }
+        const uint32_t pp = (uint32_t)(cur.i * 4 + wave), pq = (uint32_t)(cur.tq * 15 + (l32 >> 1));
+        const bool ok = (l32 & 1) && l32 < 30 && pp < PP && pq < PQ;
+        uint16_t* yp = reinterpret_cast<uint16_t*>(a.y) + (((int64_t)cur.img * PP + pp) * PQ + pq) * K + k0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {  // filters 16 j .. 16 j + 15
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v0[4 * j + e] = max_u16x2(v0[4 * j + e], up[j][e]);
+            // a lane holds filters 4 half .. + 3 of both groups of 8: the lower half takes the first
+            // group whole, the upper half the second
+            const auto s0 = __builtin_amdgcn_permlane32_swap(v0[4 * j], v0[4 * j + 2], false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(v0[4 * j + 1], v0[4 * j + 3], false, false);
+            const int f = 16 * j + 8 * half;
+            if (ok && k0 + f < K)
+                *reinterpret_cast<u32x4*>(yp + f) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+        }
+    }
+}
+
 int pow2_at_least(int v) {
     int p = 1;
     while (p < v) p <<= 1;
@@ -464,7 +659,9 @@ bool conv_thin_plan(const ConvGemmArgs& a, ThinGeom* g) {
         t.npieces = t.PH * t.ppr;
         t.ni = (t.npieces + 255) / 256;
         t.ws_bytes = ((int64_t)a.N * t.Hp * t.Wp * t.CP * 2 + 255) / 256 * 256;
-        if (t.ni > 8 || t.ws_bytes >= 0x7FFFFFF0ll) t.dma = 0;
+        if (t.ni > kMaxNi || t.ws_bytes >= 0x7FFFFFF0ll) t.dma = 0;
+        t.div_hp = make_fastdiv((uint32_t)t.Hp);
+        t.div_wp = make_fastdiv((uint32_t)t.Wp);
     }
     if (!t.dma) {
         t.PW = (TQ - 1) * a.sw + (a.S > t.T / t.CP ? a.S : t.T / t.CP);
@@ -493,6 +690,37 @@ bool conv_thin_plan(const ConvGemmArgs& a, ThinGeom* g) {
     return true;
 }
 
+// Blocks of `fn` that are resident at once, per kb blocks in grid y.
+static int64_t resident_blocks(const void* fn, int lds_bytes, int kb) {
+    int per_cu = 0, dev = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, lds_bytes) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    const int64_t cap = (int64_t)per_cu * cus / kb;
+    return cap < 1 ? 1 : cap;
+}
+
+static void launch_thin_pad(const ConvGemmArgs& a, const ThinGeom& g, hipStream_t stream) {
+    const bool x32 = a.x_f32 != 0;
+            const int64_t pix = (int64_t)a.N * g.Hp * g.Wp;
+            const dim3 pgrid((unsigned)((pix + 255) / 256));
+            uint16_t* xp = reinterpret_cast<uint16_t*>(a.partial);
+#define TBN_PAD(cp, x) hipLaunchKernelGGL((thin_pad_kernel<cp, x>), pgrid, dim3(256), 0, stream, a, g, xp)
+            switch (g.CP * 2 + (x32 ? 1 : 0)) {
+                case 2: TBN_PAD(1, false); break;
+                case 3: TBN_PAD(1, true); break;
+                case 4: TBN_PAD(2, false); break;
+                case 5: TBN_PAD(2, true); break;
+                case 8: TBN_PAD(4, false); break;
+                case 9: TBN_PAD(4, true); break;
+                case 16: TBN_PAD(8, false); break;
+                default: TBN_PAD(8, true); break;
+            }
+#undef TBN_PAD
+}
+
 hipError_t launch_conv_thin(const ConvGemmArgs& a, const ThinGeom& g, hipStream_t stream) {
     const bool x32 = a.x_f32 != 0;
     const int tt = g.T / 16;
@@ -513,21 +741,7 @@ hipError_t launch_conv_thin(const ConvGemmArgs& a, const ThinGeom& g, hipStream_
         TBN_THIN_PICK_D(8, 1) TBN_THIN_PICK_D(8, 2) TBN_THIN_PICK_D(8, 4) TBN_THIN_PICK_D(8, 8)
 #undef TBN_THIN_PICK_D
         if (!a.partial) return hipErrorInvalidValue;
-        const int64_t pix = (int64_t)a.N * g.Hp * g.Wp;
-        const dim3 pgrid((unsigned)((pix + 255) / 256));
-        uint16_t* xp = reinterpret_cast<uint16_t*>(a.partial);
-#define TBN_PAD(cp, x) hipLaunchKernelGGL((thin_pad_kernel<cp, x>), pgrid, dim3(256), 0, stream, a, g, xp)
-        switch (g.CP * 2 + (x32 ? 1 : 0)) {
-            case 2: TBN_PAD(1, false); break;
-            case 3: TBN_PAD(1, true); break;
-            case 4: TBN_PAD(2, false); break;
-            case 5: TBN_PAD(2, true); break;
-            case 8: TBN_PAD(4, false); break;
-            case 9: TBN_PAD(4, true); break;
-            case 16: TBN_PAD(8, false); break;
-            default: TBN_PAD(8, true); break;
-        }
-#undef TBN_PAD
+        launch_thin_pad(a, g, stream);
         const hipError_t pe = hipGetLastError();
         if (pe != hipSuccess) return pe;
     }
@@ -536,19 +750,79 @@ hipError_t launch_conv_thin(const ConvGemmArgs& a, const ThinGeom& g, hipStream_
         hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, g.lds_bytes) != hipSuccess)
         return hipErrorInvalidConfiguration;
     // persistent blocks: as many as can be resident at once (one round), each walking tiles
-    int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, g.lds_bytes) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                                 hipSuccess || cus < 1)
-        cus = 256;
     const int kb = (a.Kf + FB - 1) / FB;
-    int64_t cap = (int64_t)per_cu * cus / kb;
-    if (cap < 1) cap = 1;
+    const int64_t cap = resident_blocks(fn, g.lds_bytes, kb);
     const dim3 grid((unsigned)(g.ntiles < cap ? g.ntiles : cap), (unsigned)kb);
     ConvGemmArgs ka = a;
     ThinGeom kg = g;
     void* args[] = {&ka, &kg};
+    return hipLaunchKernel(fn, grid, dim3(256), args, (size_t)g.lds_bytes, stream);
+}
+
+// The fused form: layers of the zero-bordered copy (where the output is large enough for its trip through
+// memory to matter), 16-byte output rows, patches whose origin 30 output columns apart stays on 16 bytes.
+// The copy's border is one output column (sw input columns) wider on the left.
+bool conv_thin_pool_plan(const ConvGemmArgs& a, ThinGeom* g) {
+    ThinGeom t;
+    if (a.Kf % 8 != 0 || a.residual || a.y_f32 || !conv_thin_plan(a, &t) || !t.dma) return false;
+    if (t.CP < 2 || ((TQ - 2) * a.sw * t.CP * 2) % 16 != 0) return false;
+    const int step = t.CP >= 8 ? 1 : 8 / t.CP;
+    t.tiles_q = ((a.Q + 1) / 2 + 14) / 15;
+    t.Wp = (t.tiles_q - 1) * (TQ - 2) * a.sw + t.PW;
+    if (t.Wp < a.W + a.pw + a.sw) t.Wp = a.W + a.pw + a.sw;
+    t.Wp = (t.Wp + step - 1) / step * step;
+    t.ws_bytes = ((int64_t)a.N * t.Hp * t.Wp * t.CP * 2 + 255) / 256 * 256;
+    if (t.ws_bytes >= 0x7FFFFFF0ll) return false;
+    t.lds_bytes = t.s_off + 16384 + 2 * FB * 4;
+    const int nb = (a.R * a.S * a.C + 63) / 64;
+    if (t.lds_bytes > 96 * 1024 || nb * 1024 > 16384) return false;
+    t.div_hp = make_fastdiv((uint32_t)t.Hp);
+    t.div_wp = make_fastdiv((uint32_t)t.Wp);
+    *g = t;
+    return true;
+}
+
+hipError_t launch_conv_thin_pool(const ConvGemmArgs& a, const ThinGeom& plan, hipStream_t stream) {
+    ThinGeom g = plan;
+    const int tt = g.T / 16;
+    const void* fn = nullptr;
+#define TBN_THIN_POOL(cp, t) if (g.CP == cp && tt == t) fn = reinterpret_cast<const void*>(&conv_thin_pool_kernel<cp, t>);
+    TBN_THIN_POOL(2, 1) TBN_THIN_POOL(2, 2) TBN_THIN_POOL(2, 4) TBN_THIN_POOL(2, 8)
+    TBN_THIN_POOL(4, 1) TBN_THIN_POOL(4, 2) TBN_THIN_POOL(4, 4) TBN_THIN_POOL(4, 8)
+    TBN_THIN_POOL(8, 1) TBN_THIN_POOL(8, 2) TBN_THIN_POOL(8, 4) TBN_THIN_POOL(8, 8)
+#undef TBN_THIN_POOL
+    if (!fn || !a.partial) return hipErrorInvalidValue;
+    if (g.lds_bytes > 65536 &&
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, g.lds_bytes) != hipSuccess)
+        return hipErrorInvalidConfiguration;
+    const int kb = (a.Kf + FB - 1) / FB;
+    const int64_t cap = resident_blocks(fn, g.lds_bytes, kb);
+    // Segments of a column of tiles: the rounds of resident blocks times a segment's tiles and, where it
+    // does not begin at the top, the half tile of the row above; the fewest segments of equal cost.
+    const int64_t columns = (int64_t)a.N * g.tiles_q;
+    int64_t best = -1;
+    for (int segs = 1; segs <= g.tiles_p; ++segs) {
+        const int seg = (g.tiles_p + segs - 1) / segs;
+        if ((g.tiles_p + seg - 1) / seg != segs) continue;
+        const int64_t rounds = (columns * segs + cap - 1) / cap;
+        const int64_t cost = rounds * (2 * seg + (segs > 1 ? 1 : 0));
+        if (best < 0 || cost < best) {
+            best = cost;
+            g.segs = segs;
+            g.seg = seg;
+        }
+    }
+    g.ntiles = columns * g.segs;
+    if (g.ntiles + cap >= 0x7FFFFFFFll) return hipErrorInvalidValue;
+    g.div_pqt = make_fastdiv((uint32_t)(g.tiles_q * g.segs));
+    g.div_tq = make_fastdiv((uint32_t)g.tiles_q);
+    ConvGemmArgs ka = a;
+    ka.pw += ka.sw;
+    launch_thin_pad(ka, g, stream);
+    const hipError_t pe = hipGetLastError();
+    if (pe != hipSuccess) return pe;
+    const dim3 grid((unsigned)(g.ntiles < cap ? g.ntiles : cap), (unsigned)kb);
+    void* args[] = {&ka, &g};
     return hipLaunchKernel(fn, grid, dim3(256), args, (size_t)g.lds_bytes, stream);
 }
 

@@ -148,9 +148,16 @@ struct ThinGeom {
     // 16-byte pieces copied straight into LDS (ppr pieces per patch row, npieces per patch,
     // ni copy instructions per wave)
     int32_t dma, Hp, Wp, ppr, npieces, ni;
+    FastDiv div_hp, div_wp;
     int64_t ws_bytes;
+    int32_t segs, seg;  // with pooling: segments of a column of tiles, tiles of each
 };
 bool conv_thin_plan(const ConvGemmArgs& a, ThinGeom* g);
+// Convolution, ReLU and 3x3 / 2 max pooling in one kernel (false: no fused form of this layer).
+bool conv_thin_pool_plan(const ConvGemmArgs& a, ThinGeom* g);
+hipError_t launch_conv_thin_pool(const ConvGemmArgs& a, const ThinGeom& plan, hipStream_t stream);
+// ... and where the unfused layer would run the thin-input kernel, under the current tuning.
+bool conv_pool_plan(const ConvGemmArgs& a, ThinGeom* g);
 // Direct fp32-FMA kernel for small forward layers (at most 147 filter elements, C <= 8).
 bool conv_direct_eligible(const ConvGemmArgs& a);
 hipError_t launch_conv_direct(const ConvGemmArgs& a, hipStream_t stream);

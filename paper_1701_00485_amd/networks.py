@@ -94,11 +94,16 @@ class ResNet18:
         def rec(kind, layer, inp, out, res=None):
             if trace is not None:
                 trace.append((kind, layer, inp, out, res))
-        y = self.stem(x, relu=True)
-        rec("conv", self.stem, x, y)
-        p, _ = tbn.maxpool2d_fwd(y, 3, 2, 1)
-        rec("maxpool", (3, 2, 1), y, p)
-        h = p
+        # the stem and its pooling in one pass where there is one and nobody looks at what lies between
+        h = None
+        if trace is None and type(self.stem) is Conv:
+            h = tbn.conv2d_relu_maxpool_fwd(self.stem.desc(x), x, self.stem.codes, self.stem.alpha,
+                                            self.stem.scale, self.stem.bias)
+        if h is None:
+            y = self.stem(x, relu=True)
+            rec("conv", self.stem, x, y)
+            h, _ = tbn.maxpool2d_fwd(y, 3, 2, 1)
+            rec("maxpool", (3, 2, 1), y, h)
         for c1, c2, ds in self.blocks:
             a = c1(h, relu=True)
             rec("conv", c1, h, a)
