@@ -25,7 +25,8 @@ extern "C" {
 typedef enum tbn_knob {
     /* forward / backward-data GEMM family and tile shape: 0-1 register-staged fallback,
      * 10-19 LDS-DMA tile shapes, 20 thin-input kernel, 30 weight streaming, 51-55 small-layer
-     * kernel (filters per tile, waves) = (32, 4) (32, 8) (32, 16) (64, 4) (64, 8) */
+     * kernel (filters per tile, waves) = (32, 4) (32, 8) (32, 16) (64, 4) (64, 8),
+     * 60 3 x 3 layers over 64 channels */
     TBN_KNOB_CONV_TILE = 0,
     /* forward / backward-data reduction split (>= 1) */
     TBN_KNOB_CONV_SPLITS = 1,

@@ -323,12 +323,13 @@ int conv_splits_override() { return knob(KNOB_CONV_SPLITS); }
 // are few output tiles and the LDS-DMA implicit GEMM elsewhere, the direct kernel for small
 // few-channel layers, the thin-input kernel for other few-channel ones, else the general one.
 // cfg (the tile knob) forces a family: 0-1 general, 10-19 and 21-25 LDS-DMA tile shapes, 20 thin,
-// 30 weight streaming, 40 direct, 51-55 small-layer shapes.
-enum ConvPath { PATH_FC, PATH_SMALL, PATH_DMA, PATH_DIRECT, PATH_THIN, PATH_GENERIC };
+// 30 weight streaming, 40 direct, 51-55 small-layer shapes, 60 3 x 3 over 64 channels.
+enum ConvPath { PATH_FC, PATH_SMALL, PATH_C64, PATH_DMA, PATH_DIRECT, PATH_THIN, PATH_GENERIC };
 
 static ConvPath choose_path(const ConvGemmArgs& a, int cfg, FcStreamPlan* fp, ThinGeom* tg) {
     if ((cfg < 0 || cfg == 30) && fc_stream_plan(a, fp)) return PATH_FC;
     if (conv_dma_eligible(a) && conv_small_cfg(a, cfg)) return PATH_SMALL;
+    if (conv_dma_eligible(a) && conv_c64_chosen(a, cfg)) return PATH_C64;
     if (conv_dma_eligible(a) && (cfg < 0 || (cfg >= 10 && cfg < 20) || (cfg >= 21 && cfg <= 25))) return PATH_DMA;
     if ((cfg < 0 || cfg == 40) && conv_direct_eligible(a)) return PATH_DIRECT;
     if ((cfg < 0 || cfg == 20) && conv_thin_plan(a, tg)) return PATH_THIN;
@@ -341,9 +342,10 @@ size_t conv_gemm_partial_bytes(const ConvGemmArgs& a) {
     ThinGeom tg;
     switch (choose_path(a, cfg, &fp, &tg)) {
         case PATH_DMA: return plan_conv_dma(a, cfg).partial_bytes;
-        // the small-layer kernel uses none: what the tiled kernel asks for in its place, so that a
-        // layer's workspace does not depend on which of the two runs it
-        case PATH_SMALL: return cfg < 0 ? plan_conv_dma(a, cfg).partial_bytes : 0;
+        // these use none: what the tiled kernel asks for in their place, so that a layer's workspace
+        // does not depend on which of them runs it
+        case PATH_SMALL:
+        case PATH_C64: return cfg < 0 ? plan_conv_dma(a, cfg).partial_bytes : 0;
         case PATH_THIN: return tg.dma ? (size_t)tg.ws_bytes : 0;
         default: return 0;
     }
@@ -409,6 +411,7 @@ hipError_t launch_conv_gemm(const ConvGemmArgs& args, hipStream_t stream) {
     switch (choose_path(a, cfg, &fp, &tg)) {
         case PATH_FC: return launch_fc_stream(a, fp, stream);
         case PATH_SMALL: return launch_conv_small(a, conv_small_cfg(a, cfg), stream);
+        case PATH_C64: return launch_conv_c64(a, stream);
         case PATH_DMA: return launch_conv_dma(a, plan_conv_dma(a, cfg), stream);
         case PATH_DIRECT: return launch_conv_direct(a, stream);
         case PATH_THIN: return launch_conv_thin(a, tg, stream);

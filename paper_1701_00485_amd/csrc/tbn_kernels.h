@@ -132,6 +132,11 @@ hipError_t launch_conv_padded(const ConvGemmArgs& a, const ConvPadPlan& p, void*
 int conv_small_cfg(const ConvGemmArgs& a, int cfg);
 hipError_t launch_conv_small(const ConvGemmArgs& a, int cfg, hipStream_t stream);
 
+// 3 x 3 layers of stride 1 over 64 channels with many output pixels (operands and limits of the LDS-DMA
+// kernel, bf16 output); cfg 60 forces the kernel wherever it can run.
+bool conv_c64_chosen(const ConvGemmArgs& a, int cfg);
+hipError_t launch_conv_c64(const ConvGemmArgs& a, hipStream_t stream);
+
 // Forward pass for inputs with few channels (C < 8 bf16, or fp32 with C <= 8): input patch
 // and decoded filters staged in LDS with the channels padded to a power of two.
 struct ThinGeom {
