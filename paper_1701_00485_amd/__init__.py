@@ -252,6 +252,13 @@ def _numel(t, expect, name):
         raise ValueError("%s has %d elements, expected %d" % (name, t.numel(), expect))
 
 
+def _at_least(t, need, name):
+    """Operands of which the kernels use the first `need` elements: fewer would be read or written past
+    the end.  None stands for an operand that is not given."""
+    if t is not None and t.numel() < need:
+        raise ValueError("%s has %d elements, at least %d are used" % (name, t.numel(), need))
+
+
 def quantize(w: torch.Tensor, codes=None, alpha=None, counts=None, want_counts=True):
     """w: [K][n] fp32 (or [K][R][S][C]).  Returns (codes int32 words, alpha fp32, counts)."""
     out = (_native or _load_native()).quantize(w, codes, alpha, counts, want_counts)
@@ -259,6 +266,7 @@ def quantize(w: torch.Tensor, codes=None, alpha=None, counts=None, want_counts=T
         return out
     K = w.shape[0]
     n = w.numel() // K
+    _at_least(counts, 2 * K, "counts")
     pw = _dev(w, "w", (torch.float32,))
     if codes is None:
         codes = torch.empty(packed_words(K, n), dtype=torch.int32, device=w.device)
@@ -280,6 +288,7 @@ def quantize_variant(w: torch.Tensor, threshold=1.0, uniform=None, codes=None, a
     discretisation driven by `uniform` ([K][n] fp32 in [0, 1)).  Returns (codes, alpha, counts)."""
     K = w.shape[0]
     n = w.numel() // K
+    _at_least(counts, 2 * K, "counts")
     pw = _dev(w, "w", (torch.float32,))
     pu = None
     if uniform is not None:
@@ -310,6 +319,8 @@ def conv2d_fwd_noalloc(desc: ConvDesc, x, codes, alpha, y, scale=None, bias=None
     _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
     _numel(alpha, desc.k, "alpha")
     _numel(y, desc.n * P * Q * desc.k, "y")
+    _at_least(scale, desc.k, "scale")
+    _at_least(bias, desc.k, "bias")
     ep = None
     if scale is not None or bias is not None or residual is not None or relu:
         if residual is not None:
@@ -341,6 +352,8 @@ def conv2d_fwd(desc: ConvDesc, x, codes, alpha, y=None, out_dtype=torch.bfloat16
     if y is None:
         y = torch.empty((desc.n, P, Q, desc.k), dtype=out_dtype, device=x.device)
     _numel(y, desc.n * P * Q * desc.k, "y")
+    _at_least(scale, desc.k, "scale")
+    _at_least(bias, desc.k, "bias")
     ep = None
     if scale is not None or bias is not None or residual is not None or relu:
         if residual is not None:
@@ -373,6 +386,8 @@ def conv2d_relu_maxpool_fwd(desc: ConvDesc, x, codes, alpha, scale=None, bias=No
     _numel(x, desc.n * desc.h * desc.w * desc.c, "x")
     _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")
     _numel(alpha, desc.k, "alpha")
+    _at_least(scale, desc.k, "scale")
+    _at_least(bias, desc.k, "bias")
     y = torch.empty((desc.n, (P + 1) // 2, (Q + 1) // 2, desc.k), dtype=torch.bfloat16, device=x.device)
     ws = torch.empty(need.value, dtype=torch.uint8, device=x.device)
     _call("tbn_conv2d_relu_maxpool_fwd", ctypes.byref(desc), _dev(x, "x", (torch.bfloat16, torch.float32)), xt,
@@ -473,6 +488,8 @@ def conv2d_fwd_dense(desc: ConvDesc, x, w, y=None, out_dtype=torch.bfloat16, sca
     if y is None:
         y = torch.empty((desc.n, P, Q, desc.k), dtype=out_dtype, device=x.device)
     _numel(y, desc.n * P * Q * desc.k, "y")
+    _at_least(scale, desc.k, "scale")
+    _at_least(bias, desc.k, "bias")
     ep = None
     if scale is not None or bias is not None or residual is not None or relu:
         if residual is not None:
@@ -549,6 +566,7 @@ def sgd_step_quantize(w, v, g, lr, momentum=0.9, weight_decay=1e-4, codes=None, 
         return out
     K = w.shape[0]
     n = w.numel() // K
+    _at_least(counts, 2 * K, "counts")
     _numel(v, K * n, "v")
     _numel(g, K * n, "g")
     if codes is None:
@@ -599,6 +617,9 @@ def maxpool2d_bwd(dy, argmax, x_shape, k, stride, pad, out_dtype=torch.bfloat16)
     if out is not NotImplemented:
         return out
     d = PoolDesc(n, h, w, c, k, stride, pad)
+    P, Q = d.out_dims()
+    _at_least(dy, n * P * Q * c, "dy")
+    _at_least(argmax, n * P * Q * c, "argmax")
     dx = torch.empty(tuple(x_shape), dtype=out_dtype, device=dy.device)
     _call("tbn_maxpool2d_bwd", ctypes.byref(d), _dev(dy, "dy", (torch.bfloat16,)),
           _dev(argmax, "argmax", (torch.int32,)), _dev(dx, "dx"), _dtype_code(out_dtype), _stream())
@@ -635,6 +656,8 @@ def batchnorm_train_fwd(x, gamma, beta, eps=1e-5, relu=False, ws=None):
         return out
     c = x.shape[-1]
     rows = x.numel() // c
+    _at_least(gamma, c, "gamma")
+    _at_least(beta, c, "beta")
     y = torch.empty_like(x)
     mean = torch.empty(c, dtype=torch.float32, device=x.device)
     inv_std = torch.empty(c, dtype=torch.float32, device=x.device)
@@ -654,6 +677,10 @@ def batchnorm_train_bwd(x, y, dy, mean, inv_std, gamma, relu=False, ws=None, dga
         return out
     c = x.shape[-1]
     rows = x.numel() // c
+    for t, name in ((y, "y"), (dy, "dy")):
+        _at_least(t, x.numel(), name)
+    for t, name in ((mean, "mean"), (inv_std, "inv_std"), (gamma, "gamma")):
+        _at_least(t, c, name)
     dx = torch.empty_like(x)
     if dgamma is None:
         dgamma = torch.empty(c, dtype=torch.float32, device=x.device)
@@ -661,11 +688,12 @@ def batchnorm_train_bwd(x, y, dy, mean, inv_std, gamma, relu=False, ws=None, dga
         dbeta = torch.empty(c, dtype=torch.float32, device=x.device)
     _numel(dgamma, c, "dgamma")
     _numel(dbeta, c, "dbeta")
+    f32 = (torch.float32,)
     ws = _bn_ws(rows, c, ws, x.device)
     _call("tbn_batchnorm_train_bwd", _dev(x, "x", (torch.bfloat16,)), _dev(y, "y", (torch.bfloat16,)),
-          _dev(dy, "dy", (torch.bfloat16,)), rows, c, 1 if relu else 0, _dev(mean, "mean"),
-          _dev(inv_std, "inv_std"), _dev(gamma, "gamma"), _dev(dgamma, "dgamma"), _dev(dbeta, "dbeta"),
-          _dev(dx, "dx"), _dev(ws, "ws"), ws.numel() * ws.element_size(), _stream())
+          _dev(dy, "dy", (torch.bfloat16,)), rows, c, 1 if relu else 0, _dev(mean, "mean", f32),
+          _dev(inv_std, "inv_std", f32), _dev(gamma, "gamma", f32), _dev(dgamma, "dgamma", f32),
+          _dev(dbeta, "dbeta", f32), _dev(dx, "dx"), _dev(ws, "ws"), ws.numel() * ws.element_size(), _stream())
     return dx, dgamma, dbeta
 
 
@@ -673,6 +701,7 @@ def relu_bwd(y, dy):
     out = (_native or _load_native()).relu_bwd(y, dy)
     if out is not NotImplemented:
         return out
+    _at_least(y, dy.numel(), "y")
     dx = torch.empty_like(dy)
     _call("tbn_relu_bwd", _dev(y, "y", (torch.bfloat16,)), _dev(dy, "dy", (torch.bfloat16,)), dy.numel(),
           _dev(dx, "dx"), _stream())
@@ -685,6 +714,7 @@ def softmax_xent(logits, labels):
     if out is not NotImplemented:
         return out
     n, k = logits.shape
+    _at_least(labels, n, "labels")
     loss = torch.empty(1, dtype=torch.float32, device=logits.device)
     per = torch.empty(n, dtype=torch.float32, device=logits.device)
     dz = torch.empty((n, k), dtype=torch.bfloat16, device=logits.device)

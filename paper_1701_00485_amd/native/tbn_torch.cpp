@@ -37,9 +37,10 @@ const at::Tensor* dense(PyObject* o) {
     return t.is_contiguous() ? &t : nullptr;
 }
 
-const at::Tensor* dense(PyObject* o, at::ScalarType type) {
+// ... of this type, with at least `need` elements (the kernels use the first `need`).
+const at::Tensor* dense(PyObject* o, at::ScalarType type, int64_t need = 0) {
     const at::Tensor* t = dense(o);
-    return t && t->scalar_type() == type ? t : nullptr;
+    return t && t->scalar_type() == type && t->numel() >= need ? t : nullptr;
 }
 
 bool float_type(const at::Tensor& t, tbn_dtype* out) {
@@ -190,19 +191,20 @@ PyObject* none() {
 struct Ep {
     tbn_epilogue e = {};
     bool any = false;
-    bool get(PyObject* scale, PyObject* bias, PyObject* residual, PyObject* relu, int64_t y_numel, at::ScalarType yt) {
+    bool get(PyObject* scale, PyObject* bias, PyObject* residual, PyObject* relu, int32_t k, int64_t y_numel,
+             at::ScalarType yt) {
         bool r;
         if (!truth(relu, &r)) return false;
         e.relu = r ? 1 : 0;
         any = r;
         if (scale != Py_None) {
-            const at::Tensor* t = dense(scale, at::kFloat);
+            const at::Tensor* t = dense(scale, at::kFloat, k);
             if (!t) return false;
             e.scale = f32(*t);
             any = true;
         }
         if (bias != Py_None) {
-            const at::Tensor* t = dense(bias, at::kFloat);
+            const at::Tensor* t = dense(bias, at::kFloat, k);
             if (!t) return false;
             e.bias = f32(*t);
             any = true;
@@ -243,7 +245,7 @@ PyObject* conv2d_fwd(PyObject*, PyObject* const* v, Py_ssize_t n) {
     Ep ep;
     Ws ws;
     if (x->numel() != d.x_numel() || codes->numel() != d.words() || alpha->numel() != d.d.k ||
-        !y.take(v[4], yt, d.y_numel()) || !ep.get(v[6], v[7], v[8], v[9], d.y_numel(), yt) || !ws.take(v[10]))
+        !y.take(v[4], yt, d.y_numel()) || !ep.get(v[6], v[7], v[8], v[9], d.d.k, d.y_numel(), yt) || !ws.take(v[10]))
         return declined();
     size_t need = 0;
     if (!ws.given && tbn_workspace_size(TBN_OP_FWD, &d.d, &need) != TBN_OK) return declined();
@@ -271,7 +273,7 @@ PyObject* conv2d_fwd_dense(PyObject*, PyObject* const* v, Py_ssize_t n) {
     Out y;
     Ep ep;
     if (x->numel() != d.x_numel() || w->numel() != d.w_numel() || !y.take(v[3], yt, d.y_numel()) ||
-        !ep.get(v[5], v[6], v[7], v[8], d.y_numel(), yt))
+        !ep.get(v[5], v[6], v[7], v[8], d.d.k, d.y_numel(), yt))
         return declined();
     y.make({d.d.n, d.p, d.q, d.d.k}, yt, *x);
     void *xp = x->data_ptr(), *yp = y.t.data_ptr();
@@ -385,8 +387,8 @@ struct Filters {
         k = w.size(0);
         n = w.numel() / k;
         want = wanted || pn != Py_None;
-        if (pn != Py_None) {  // any size: as the Python code takes it
-            const at::Tensor* t = dense(pn, at::kInt);
+        if (pn != Py_None) {  // any size that holds the counts
+            const at::Tensor* t = dense(pn, at::kInt, 2 * k);
             if (!t || !counts.take(pn, at::kInt, t->numel())) return false;
         }
         return codes.take(pc, at::kInt, tbn_packed_words(k, n)) && alpha.take(pa, at::kFloat, k);
@@ -555,8 +557,9 @@ PyObject* batchnorm_train_fwd(PyObject*, PyObject* const* v, Py_ssize_t n) {
     bool relu;
     Ws ws;
     size_t need = 0;
-    if (!x || !gamma || !beta || !rows_of(*x, &rows, &c) || !number(v[3], &eps) || !truth(v[4], &relu) ||
-        !ws.take(v[5]) || tbn_batchnorm_workspace_size(rows, c, &need) != TBN_OK)
+    if (!x || !gamma || !beta || !rows_of(*x, &rows, &c) || gamma->numel() < c || beta->numel() < c ||
+        !number(v[3], &eps) || !truth(v[4], &relu) || !ws.take(v[5]) ||
+        tbn_batchnorm_workspace_size(rows, c, &need) != TBN_OK)
         return declined();
     Out y, mean, inv;
     y.make(x->sizes(), at::kBFloat16, *x);
@@ -585,8 +588,10 @@ PyObject* batchnorm_train_bwd(PyObject*, PyObject* const* v, Py_ssize_t n) {
     Ws ws;
     size_t need = 0;
     Out dx, dgamma, dbeta;
-    if (!x || !y || !dy || !mean || !inv || !gamma || !rows_of(*x, &rows, &c) || !truth(v[6], &relu) ||
-        !ws.take(v[7]) || !dgamma.take(v[8], at::kFloat, c) || !dbeta.take(v[9], at::kFloat, c) ||
+    if (!x || !y || !dy || !mean || !inv || !gamma || !rows_of(*x, &rows, &c) ||
+        y->numel() < x->numel() || dy->numel() < x->numel() || mean->numel() < c || inv->numel() < c ||
+        gamma->numel() < c || !truth(v[6], &relu) || !ws.take(v[7]) ||
+        !dgamma.take(v[8], at::kFloat, c) || !dbeta.take(v[9], at::kFloat, c) ||
         tbn_batchnorm_workspace_size(rows, c, &need) != TBN_OK)
         return declined();
     dx.make(x->sizes(), at::kBFloat16, *x);
@@ -608,7 +613,7 @@ PyObject* relu_bwd(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     TBN_ARGS(2);
     const at::Tensor *y = dense(v[0], at::kBFloat16), *dy = dense(v[1], at::kBFloat16);
-    if (!y || !dy) return declined();
+    if (!y || !dy || y->numel() < dy->numel()) return declined();
     Out dx;
     dx.make(dy->sizes(), at::kBFloat16, *dy);
     void *yp = y->data_ptr(), *dyp = dy->data_ptr(), *dxp = dx.t.data_ptr();
@@ -622,7 +627,8 @@ PyObject* softmax_xent(PyObject*, PyObject* const* v, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     TBN_ARGS(2);
     const at::Tensor *z = dense(v[0], at::kFloat), *labels = dense(v[1], at::kInt);
-    if (!z || !labels || z->dim() != 2 || z->size(0) != (int32_t)z->size(0) || z->size(1) != (int32_t)z->size(1))
+    if (!z || !labels || z->dim() != 2 || z->size(0) != (int32_t)z->size(0) || z->size(1) != (int32_t)z->size(1) ||
+        labels->numel() < z->size(0))
         return declined();
     Out loss, per, dz;
     loss.make({1}, at::kFloat, *z);
@@ -650,6 +656,8 @@ PyObject* maxpool2d_bwd(PyObject*, PyObject* const* v, Py_ssize_t n) {
         return declined();
     int32_t p, q;
     if (tbn_pool_out_dims(&d, &p, &q) != TBN_OK) return declined();
+    const int64_t windows = (int64_t)d.n * p * q * d.c;
+    if (dy->numel() < windows || arg->numel() < windows) return declined();
     Out dx;
     dx.make({d.n, d.h, d.w, d.c}, xt, *dy);
     void *dyp = dy->data_ptr(), *dxp = dx.t.data_ptr();
