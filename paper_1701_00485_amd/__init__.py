@@ -2,12 +2,14 @@
 
 A thin ctypes layer over the C ABI in ``include/tbn.h``.  It only marshals arguments:
 torch supplies device memory and the current stream, and every step of the computation
-runs in the library's HIP kernels.  If ``libtbn.so`` or ``_tbn_torch.so`` is missing or does
-not load, every call raises; there is no fallback.
+runs in the library's HIP kernels.  If ``libtbn.so`` is missing or does not load, every call
+raises; there is no fallback.
 
 Ordinary calls (plain dense GPU tensors of the expected types and sizes) are marshalled in
 native code (``native/tbn_torch.cpp``), which declines everything else; what it declines takes
-the ctypes code below, whose checks raise the errors.
+the ctypes code below, whose checks raise the errors.  So does every call, after one warning, where
+that module (``_tbn_torch.so``, bound to one torch build) is missing or does not load: the same
+kernels with more host time per call.
 
 Calls (same names as the C ABI, without the ``tbn_`` prefix):
   quantize(w)                      Sec. 2 Eq. (3)-(5)   -> packed codes, alpha, counts
@@ -23,6 +25,8 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import sys
+import warnings
 
 import torch
 
@@ -123,16 +127,30 @@ def load():
     return lib
 
 
+class _NoBinding:
+    """In the native module's place where it does not load: declines every call."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
+
+
 def _load_native():
-    """The native marshalling module (built in-tree by build.py); raises if it is missing."""
+    """The native marshalling module (built in-tree by build.py); _NoBinding, with a warning, where it is
+    missing, does not load or was built for another torch or Python."""
     global _native
     load()
-    if not os.path.exists(BINDING_PATH):
-        raise RuntimeError("_tbn_torch.so not built: run `python -c 'import __graft_entry__ as g; g.build()'`")
-    spec = importlib.util.spec_from_file_location("_tbn_torch", BINDING_PATH)
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
-    mod.bind_types(ConvDesc, TbnError)
+    try:
+        spec = importlib.util.spec_from_file_location("_tbn_torch", BINDING_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        here = "torch %s, Python %d.%d" % ((torch.__version__,) + sys.version_info[:2])
+        if mod.BUILT_FOR != here:
+            raise ImportError("built for %s, this is %s" % (mod.BUILT_FOR, here))
+        mod.bind_types(ConvDesc, TbnError)
+    except (ImportError, OSError) as e:
+        warnings.warn("_tbn_torch.so not loaded (%s): calls are marshalled by ctypes, at several times the host time "
+                      "per call; run `python -c 'import __graft_entry__ as g; g.build()'`" % e)
+        mod = _NoBinding()
     _native = mod
     return mod
 

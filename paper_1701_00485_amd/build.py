@@ -52,7 +52,8 @@ def _compile_binding():
     includes = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"]] + cpp_extension.include_paths()
     includes.append(os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"))
     cmd = [HIPCC, "-x", "c++", "-O2", "-fPIC", "-std=c++17", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           '-DTBN_TORCH_VERSION="%s"' % torch.__version__]
     for i in includes:
         cmd += ["-isystem" if "torch" in i else "-I", i]
     r = subprocess.run(cmd + ["-c", src, "-o", obj], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

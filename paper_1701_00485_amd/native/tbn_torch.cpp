@@ -688,4 +688,16 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tbn_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__tbn_torch(void) { return PyModule_Create(&module); }
+#define TBN_STR2(x) #x
+#define TBN_STR(x) TBN_STR2(x)
+
+PyMODINIT_FUNC PyInit__tbn_torch(void) {
+    PyObject* m = PyModule_Create(&module);
+    // the module uses torch's and Python's C++ types directly: the package looks at this before any call
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", "torch " TBN_TORCH_VERSION ", Python " TBN_STR(PY_MAJOR_VERSION) "."
+                                                        TBN_STR(PY_MINOR_VERSION)) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
