@@ -35,6 +35,7 @@ LIB_PATH = os.path.join(_HERE, "libtbn.so")
 BINDING_PATH = os.path.join(_HERE, "_tbn_torch.so")
 
 TBN_BF16, TBN_F32 = 0, 1
+TBN_ERR_UNSUPPORTED = 3
 OP_FWD, OP_BWD_DATA, OP_BWD_WEIGHT = 0, 1, 2
 
 _lib = None
@@ -398,8 +399,12 @@ def conv2d_relu_maxpool_fwd(desc: ConvDesc, x, codes, alpha, scale=None, bias=No
     layer has no fused form (few channels, large input only: see tbn_conv2d_relu_maxpool_fwd)."""
     need = ctypes.c_size_t()
     xt = _dtype_code(x.dtype)
-    if load().tbn_conv2d_relu_maxpool_workspace_size(ctypes.byref(desc), xt, ctypes.byref(need)):
-        return None
+    try:
+        _call("tbn_conv2d_relu_maxpool_workspace_size", ctypes.byref(desc), xt, ctypes.byref(need))
+    except TbnError as e:
+        if e.status == TBN_ERR_UNSUPPORTED:
+            return None
+        raise
     P, Q = desc.out_dims()
     _numel(x, desc.n * desc.h * desc.w * desc.c, "x")
     _numel(codes, packed_words(desc.k, desc.r * desc.s * desc.c), "codes")

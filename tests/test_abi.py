@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import oracle
 import paper_1701_00485_amd as tbn
@@ -245,3 +246,13 @@ def test_unknown_dtype_and_pool_geometry():
     pd = tbn.PoolDesc(1, 2, 2, 8, 3, 1, 0)  # window larger than the input
     p, q = ctypes.c_int32(), ctypes.c_int32()
     assert lib.tbn_pool_out_dims(ctypes.byref(pd), ctypes.byref(p), ctypes.byref(q)) == 2
+
+
+def test_fused_stem_reports_errors():
+    # None only where the layer has no fused form; an invalid geometry is an error, as in the separate calls
+    x = torch.zeros(1, dtype=torch.bfloat16)
+    assert tbn.conv2d_relu_maxpool_fwd(tbn.ConvDesc(2, 7, 6, 16, 24, 3, 3, 1, 1), x, x, x) is None
+    for g in ((0, 224, 224, 3, 64, 7, 7, 2, 3), (64, 224, 224, 3, 64, 7, 7, 0, 3), (64, 4, 4, 3, 64, 7, 7, 2, 0)):
+        with pytest.raises(tbn.TbnError) as e:
+            tbn.conv2d_relu_maxpool_fwd(tbn.ConvDesc(*g), x, x, x)
+        assert e.value.status == 2
