@@ -314,9 +314,12 @@ int conv_code8_tile(int32_t N, int32_t P, int32_t Q, int32_t K, int64_t n) {
     if (b1 <= 512) return nst >= 12 && b2 <= 256 ? 8 : 5;
     int cfg = K > 128 ? 1 : (K > 64 ? 2 : 3);
     const int bm = 128, bn = cfg == 1 ? 256 : (cfg == 2 ? 128 : 64);
-    // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles (also below 128 filters:
-    // 20 x 20 x 336 -> 78 at batch 32 25.0 / 20.3 -> 18.5 / 15.8)
-    if (((M + bm - 1) / bm) * ((K + bn - 1) / bn) < 384) cfg = 4;
+    // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles beyond 64 filters.  Measured at
+    // 18 k to 48 k rows, reductions of 256 to 10000: 72 to 120 filters 0.88-1.01 (int8) and 0.83-0.93 (fp8)
+    // of the 128-filter tile's time (3 x 3 over 128 channels, 32 k rows, 96 filters 11.5 / 10.3 -> 10.8 /
+    // 9.1 us); 16 to 64 filters 1.06-1.30 and 1.01-1.28 of the 64-filter tile's (64 filters 9.0 / 8.1 there,
+    // 10.6 / 8.8 with 64 x 128, half of whose waves work on filters that do not exist)
+    if (((M + bm - 1) / bm) * ((K + bn - 1) / bn) < 384 && K > 64) cfg = 4;
     return cfg;
 }
 

@@ -21,11 +21,15 @@ CASES = [(1, 1, 1, 16, 1, 1, 1, 1, 0), (1, 1, 31, 16, 32, 1, 1, 1, 0), (1, 1, 33
          (2, 5, 7, 48, 66, 3, 3, 1, 1), (1, 7, 7, 128, 100, 3, 3, 2, 1), (3, 4, 4, 80, 31, 5, 5, 1, 2),
          (2, 6, 5, 192, 65, 3, 1, 1, 2), (1, 9, 9, 16, 96, 7, 7, 1, 3), (1, 3, 3, 1024, 40, 3, 3, 1, 1)]
 
+# ... and where the built-in choice changes beyond them: 64 and 65 filters with fewer than 384 tiles, and with more
+RULE = [(1, 131, 129, 16, 64, 1, 1, 1, 0), (1, 131, 129, 16, 65, 1, 1, 1, 0), (1, 131, 129, 16, 31, 3, 3, 1, 1),
+        (1, 222, 223, 16, 64, 1, 1, 1, 0), (1, 222, 223, 16, 65, 1, 1, 1, 0)]
+
 
 @pytest.mark.parametrize("tile", [-1, 5, 6, 7, 8])
 def test_small_layers_8bit(tbn, tile, knobs):
     knobs(i8_tile=tile, fp8_tile=tile)
-    for g in CASES:
+    for g in CASES + (RULE if tile < 0 else []):
         for out, relu in (("f32", False), ("bf16", True)):
             log("small 8-bit layer %s shape %d %s" % (g, tile, out))
             d, xq, codes, alpha, words, x_scale = i8._problem(g, 4)
