@@ -379,11 +379,11 @@ __global__ __launch_bounds__(256) void avgpool8_kernel(int32_t N, int32_t HW, in
 //     load per row each); the 256 threads cover tpr = 256 / groups rows at a time, four such steps'
 //     loads issued together, then combine their row lanes through LDS in a fixed order and write
 //     partial[b][c];
-//   * finalize: 64 threads per channel add partial[0..chunks)[c] in a fixed order.
+//   * finalize: 16 or 64 threads per channel add partial[0..chunks)[c] in a fixed order.
 // Then the element-wise passes, with the same thread layout, so that a thread keeps the factors of
 // its 8 channels in registers over its rows.  (A thread per 16 bytes, loading them for every 8 values,
-// issued three to ten loads of factors per load of data: 28.2 us for the backward pass over 131072 x 128
-// against 23.2, 14.0 for the forward pass against 13.1.)
+// issued three to ten loads of factors per load of data: 28.5 us for the backward pass over 131072 x 128
+// against 21.0, 14.4 for the forward pass against 11.1.)  Small tensors take one row a thread, for more blocks.
 //
 // C % 8 != 0 (up to 256 channels, large tensors): eight consecutive rows are C groups of 8 values whose channels
 // (8 g + e) % C repeat every eight rows, so the same code runs over "rows" of 8 C values (FLAT); the last
@@ -437,6 +437,33 @@ struct BnLane {
     }
 };
 
+// The factors of a thread's NV channels in the element-wise passes: f[j][e] = src[j][channel e].  FLAT: through
+// LDS, as a thread's channels follow no vector load and 32 to 40 gathered loads of 4 bytes bound the pass
+// (10039 x 252: 10.9 and 14.6 us forward and backward with them).  All threads of the block call it.
+template <int KIND, int NF>
+__device__ __forceinline__ void bn_factors(const BnLane<KIND>& l, int32_t C, const float* const (&src)[NF],
+                                           float (&f)[NF][BnLane<KIND>::NV]) {
+    if constexpr (KIND == BN_FLAT) {
+        constexpr int PITCH = 33;  // channel c at 33 (c % 8) + c / 8: neighbours' channels, 8 apart, in different banks
+        __shared__ float sh[NF][8 * PITCH];
+        if ((int)threadIdx.x < C)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) sh[j][(threadIdx.x & 7) * PITCH + (threadIdx.x >> 3)] = src[j][threadIdx.x];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int c = l.channel(e, C);
+#pragma unroll
+            for (int j = 0; j < NF; ++j) f[j][e] = sh[j][(c & 7) * PITCH + (c >> 3)];
+        }
+    } else if (l.active) {
+#pragma unroll
+        for (int e = 0; e < BnLane<KIND>::NV; ++e)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) f[j][e] = src[j][l.channel(e, C)];
+    }
+}
+
 template <int MODE, int KIND>
 __global__ __launch_bounds__(256) void bn_partial_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ y,
                                                          const uint16_t* __restrict__ dy, int64_t rows, int32_t C,
@@ -489,15 +516,20 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const uint16_t* __restr
 #pragma unroll
             for (int u = 0; u < UN; ++u) add(xv[u], dv[u], yv[u]);
         }
-        for (; r < rend; r += l.tpr) {
-            float xv[NV], dv[NV], yv[NV];
-            const int64_t i = r * l.width + l.col;
-            load_values<NV>(x + i, xv);
-            if constexpr (MODE == BN_BWD) {
-                load_values<NV>(dy + i, dv);
-                load_values<NV>(y + i, yv);
+        if (r < rend) {  // the rest together, past the end the last row again and not added
+            float xv[UN - 1][NV], dv[UN - 1][NV], yv[UN - 1][NV];
+#pragma unroll
+            for (int u = 0; u < UN - 1; ++u) {
+                const int64_t i = min(r + u * l.tpr, rend - 1) * l.width + l.col;
+                load_values<NV>(x + i, xv[u]);
+                if constexpr (MODE == BN_BWD) {
+                    load_values<NV>(dy + i, dv[u]);
+                    load_values<NV>(y + i, yv[u]);
+                }
             }
-            add(xv, dv, yv);
+#pragma unroll
+            for (int u = 0; u < UN - 1; ++u)
+                if (r + u * l.tpr < rend) add(xv[u], dv[u], yv[u]);
         }
     }
     const int W = l.Gs * NV;  // values of this slice
@@ -509,17 +541,19 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const uint16_t* __restr
         }
     }
     __syncthreads();
-    // The row lanes of each value (parts of them by different threads where there are fewer than 256
-    // values), then the parts, FLAT: of a channel's eight places in the 8 C values; in fixed order.
-    // Two short loops: one over everything by as many threads as there are channels is a chain of up
-    // to 256 LDS reads (5 us for 17 channels).
-    const int parts = W < 256 ? 256 / W : 1;
-    const int lanes = min(parts, l.tpr);
-    for (int q0 = 0; q0 < W; q0 += 256) {
+    // The row lanes of each value, FLAT: and a channel's eight places in the 8 C values; in fixed order.
+    // One loop over them by as many threads as there are channels is a chain of up to 256 LDS reads
+    // (5 us for 17 channels): with FLAT, and where four threads or more share a value, the row lanes are
+    // first reduced to at most 16 parts.  Elsewhere that would only add barriers (109 x 1952: 4.5 us without,
+    // 7.1 with; 9000 x 128, two threads a value: 3.8 and 4.1).
+    const int parts = W < 256 ? min(256 / W, 16) : 1;
+    const bool reduce = parts < l.tpr && (KIND == BN_FLAT || parts >= 4);
+    const int lanes = reduce ? parts : l.tpr;
+    for (int q0 = 0; reduce && q0 < W; q0 += 256) {
         const int q = q0 + (parts > 1 ? (int)threadIdx.x % W : (int)threadIdx.x);
         const int part = parts > 1 ? (int)threadIdx.x / W : 0;
         float u1 = 0.0f, u2 = 0.0f;
-        if (q < W && part < lanes) {
+        if (q < W && part < parts) {
 #pragma unroll 4
             for (int rr = part; rr < l.tpr; rr += parts) {
                 u1 += s1[rr * W + q];
@@ -527,7 +561,7 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const uint16_t* __restr
             }
         }
         __syncthreads();
-        if (q < W && part < lanes) {
+        if (q < W && part < parts) {
             s1[part * W + q] = u1;
             s2[part * W + q] = u2;
         }
@@ -563,40 +597,46 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const uint16_t* __restr
     }
 }
 
-// Sums over the chunks of 16 channels: 64 chunk lanes per channel (each adds every 64th chunk in order,
-// eight loads in flight), combined four by four: within the waves by a fixed butterfly, then over the
-// waves.  T: the sums' type.
+// Sums over the chunks of 16 channels: LANES chunk lanes per channel (each adds every LANES-th chunk in
+// order, eight loads in flight), combined in a fixed order: within the waves by a butterfly over their
+// four chunk lanes, then over the waves four by four.  T: the sums' type.
 template <typename T>
 __device__ __forceinline__ T four_lanes(T u) {  // over the wave's four chunk lanes of a channel
     u += __shfl_xor(u, 16, kWave);
     return u + __shfl_xor(u, 32, kWave);
 }
 
-template <typename T>
+template <int LANES, typename T>
 __device__ __forceinline__ bool bn_chunk_sums(const float* __restrict__ p1, const float* __restrict__ p2, int64_t chunks,
                                               int32_t C, int* channel, T* t1, T* t2) {
-    constexpr int LANES = 64;
-    __shared__ T s1[16][16], s2[16][16];
+    __shared__ T s1[LANES / 4][16], s2[LANES / 4][16];
     const int cl = threadIdx.x & 15, part = threadIdx.x >> 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = (int)blockIdx.x * 16 + cl;
     T u1 = 0, u2 = 0;
     if (c < C) {
-        for (int64_t b = part; b < chunks; b += 8 * LANES) {
-            float v1[8], v2[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                // (the last chunk's again past the end, not added below: a load under a condition waits
-                // for the one before it)
-                const int64_t at = min(b + LANES * k, chunks - 1) * C + c;
-                v1[k] = p1[at];
-                v2[k] = p2[at];
+        if (chunks <= LANES) {
+            if (part < chunks) {
+                u1 = (T)p1[part * C + c];
+                u2 = (T)p2[part * C + c];
             }
+        } else {
+            for (int64_t b = part; b < chunks; b += 8 * LANES) {
+                float v1[8], v2[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const bool in = b + LANES * k < chunks;
-                u1 += in ? (T)v1[k] : (T)0;
-                u2 += in ? (T)v2[k] : (T)0;
+                for (int k = 0; k < 8; ++k) {
+                    // (the last chunk's again past the end, not added below: a load under a condition
+                    // waits for the one before it)
+                    const int64_t at = min(b + LANES * k, chunks - 1) * C + c;
+                    v1[k] = p1[at];
+                    v2[k] = p2[at];
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const bool in = b + LANES * k < chunks;
+                    u1 += in ? (T)v1[k] : (T)0;
+                    u2 += in ? (T)v2[k] : (T)0;
+                }
             }
         }
     }
@@ -608,20 +648,28 @@ __device__ __forceinline__ bool bn_chunk_sums(const float* __restrict__ p1, cons
     }
     __syncthreads();
     if (wave > 0) return false;
-    const int w4 = 4 * (lane >> 4);
-    *t1 = four_lanes((s1[w4][cl] + s1[w4 + 1][cl]) + (s1[w4 + 2][cl] + s1[w4 + 3][cl]));
-    *t2 = four_lanes((s2[w4][cl] + s2[w4 + 1][cl]) + (s2[w4 + 2][cl] + s2[w4 + 3][cl]));
+    if constexpr (LANES == 16) {
+        *t1 = (s1[0][cl] + s1[1][cl]) + (s1[2][cl] + s1[3][cl]);
+        *t2 = (s2[0][cl] + s2[1][cl]) + (s2[2][cl] + s2[3][cl]);
+    } else {
+        static_assert(LANES == 64, "sixteen waves");
+        const int w4 = 4 * (lane >> 4);
+        *t1 = four_lanes((s1[w4][cl] + s1[w4 + 1][cl]) + (s1[w4 + 2][cl] + s1[w4 + 3][cl]));
+        *t2 = four_lanes((s2[w4][cl] + s2[w4 + 1][cl]) + (s2[w4 + 2][cl] + s2[w4 + 3][cl]));
+    }
     *channel = c;
     return lane < 16 && c < C;
 }
 
 // Backward sums dbeta = sum g and dgamma = sum g * xhat.
-__global__ __launch_bounds__(1024) void bn_bwd_finalize_kernel(const float* __restrict__ p1,
-                                                               const float* __restrict__ p2, int64_t chunks, int32_t C,
-                                                               float* __restrict__ out1, float* __restrict__ out2) {
+template <int LANES>
+__global__ __launch_bounds__(16 * LANES) void bn_bwd_finalize_kernel(const float* __restrict__ p1,
+                                                                     const float* __restrict__ p2, int64_t chunks,
+                                                                     int32_t C, float* __restrict__ out1,
+                                                                     float* __restrict__ out2) {
     int c;
     float t1, t2;
-    if (!bn_chunk_sums(p1, p2, chunks, C, &c, &t1, &t2)) return;
+    if (!bn_chunk_sums<LANES>(p1, p2, chunks, C, &c, &t1, &t2)) return;
     out1[c] = t1;  // dbeta
     out2[c] = t2;  // dgamma
 }
@@ -629,13 +677,16 @@ __global__ __launch_bounds__(1024) void bn_bwd_finalize_kernel(const float* __re
 // One-pass statistics: the chunk sums S1 = sum d, S2 = sum d^2 (d = x - x[0][c]) added in fp64, then
 // mean = x[0][c] + S1 / n and inv_std = 1 / sqrt(S2 / n - (S1 / n)^2 + eps) (biased variance,
 // clamped at zero).
-__global__ __launch_bounds__(1024) void bn_stats_finalize_kernel(const float* __restrict__ p1,
-                                                                 const float* __restrict__ p2, int64_t chunks, int32_t C,
-                                                                 int64_t rows, float eps, const uint16_t* __restrict__ x,
-                                                                 float* __restrict__ mean, float* __restrict__ inv_std) {
+template <int LANES>
+__global__ __launch_bounds__(16 * LANES) void bn_stats_finalize_kernel(const float* __restrict__ p1,
+                                                                       const float* __restrict__ p2, int64_t chunks,
+                                                                       int32_t C, int64_t rows, float eps,
+                                                                       const uint16_t* __restrict__ x,
+                                                                       float* __restrict__ mean,
+                                                                       float* __restrict__ inv_std) {
     int c;
     double t1, t2;
-    if (!bn_chunk_sums(p1, p2, chunks, C, &c, &t1, &t2)) return;
+    if (!bn_chunk_sums<LANES>(p1, p2, chunks, C, &c, &t1, &t2)) return;
     const double n = (double)rows;
     const double d1 = t1 / n;
     double var = t2 / n - d1 * d1;
@@ -644,10 +695,9 @@ __global__ __launch_bounds__(1024) void bn_stats_finalize_kernel(const float* __
     inv_std[c] = 1.0f / sqrtf((float)var + eps);
 }
 
-constexpr int kBnRows = 4;  // rows per thread of the element-wise passes
 
 // y = act(gamma * (x - mean) * inv_std + beta)
-template <int KIND>
+template <int KIND, int ROWS>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const uint16_t* __restrict__ x, int64_t rows, int32_t C,
                                                        const float* __restrict__ mean, const float* __restrict__ inv_std,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -665,28 +715,21 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const uint16_t* __restric
             y[i] = (uint16_t)f32_to_bf16_bits(act(bf16_bits_to_f32(x[i]), mean[c], inv_std[c], gamma[c], beta[c]));
         }
     }
-    if (!l.active) return;
     const int64_t srows = KIND == BN_FLAT ? rows / 8 : rows;
-    const int64_t r = (int64_t)blockIdx.x * (kBnRows * l.tpr) + l.r0;
-    float v[kBnRows][NV];
+    const int64_t r = (int64_t)blockIdx.x * (ROWS * l.tpr) + l.r0;
+    float v[ROWS][NV];
+    // (past the end the last row again: a load under a condition waits for the one before it)
 #pragma unroll
-    for (int u = 0; u < kBnRows; ++u)
-        if (r + u * l.tpr < srows) load_values<NV>(x + (r + u * l.tpr) * l.width + l.col, v[u]);
-    float m[NV], is[NV], ga[NV], be[NV];
+    for (int u = 0; u < ROWS; ++u) load_values<NV>(x + min(r + u * l.tpr, srows - 1) * l.width + l.col, v[u]);
+    float f[4][NV];
+    bn_factors<KIND, 4>(l, C, {mean, inv_std, gamma, beta}, f);
+    if (!l.active) return;
 #pragma unroll
-    for (int e = 0; e < NV; ++e) {
-        const int c = l.channel(e, C);
-        m[e] = mean[c];
-        is[e] = inv_std[c];
-        ga[e] = gamma[c];
-        be[e] = beta[c];
-    }
-#pragma unroll
-    for (int u = 0; u < kBnRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
         if (r + u * l.tpr >= srows) break;
         uint16_t* const o = y + (r + u * l.tpr) * l.width + l.col;
 #pragma unroll
-        for (int e = 0; e < NV; ++e) v[u][e] = act(v[u][e], m[e], is[e], ga[e], be[e]);
+        for (int e = 0; e < NV; ++e) v[u][e] = act(v[u][e], f[0][e], f[1][e], f[2][e], f[3][e]);
         if constexpr (NV == 8)
             *reinterpret_cast<u32x4*>(o) = u32x4{pack_bf16x2(v[u][0], v[u][1]), pack_bf16x2(v[u][2], v[u][3]),
                                                  pack_bf16x2(v[u][4], v[u][5]), pack_bf16x2(v[u][6], v[u][7])};
@@ -696,7 +739,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const uint16_t* __restric
 }
 
 // dx = gamma * inv_std * (g - dbeta / rows - xhat * dgamma / rows)
-template <int KIND>
+template <int KIND, int ROWS>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ y,
                                                            const uint16_t* __restrict__ dy, int64_t rows, int32_t C,
                                                            int relu, const float* __restrict__ mean,
@@ -721,36 +764,27 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const uint16_t* __res
                                                     dgamma[c]));
         }
     }
-    if (!l.active) return;
     const int64_t srows = KIND == BN_FLAT ? rows / 8 : rows;
-    const int64_t r = (int64_t)blockIdx.x * (kBnRows * l.tpr) + l.r0;
-    float xv[kBnRows][NV], yv[kBnRows][NV], dv[kBnRows][NV];
+    const int64_t r = (int64_t)blockIdx.x * (ROWS * l.tpr) + l.r0;
+    float xv[ROWS][NV], yv[ROWS][NV], dv[ROWS][NV];
 #pragma unroll
-    for (int u = 0; u < kBnRows; ++u) {
-        if (r + u * l.tpr < srows) {
-            const int64_t i = (r + u * l.tpr) * l.width + l.col;
-            load_values<NV>(x + i, xv[u]);
-            load_values<NV>(y + i, yv[u]);
-            load_values<NV>(dy + i, dv[u]);
-        }
+    for (int u = 0; u < ROWS; ++u) {
+        const int64_t i = min(r + u * l.tpr, srows - 1) * l.width + l.col;
+        load_values<NV>(x + i, xv[u]);
+        load_values<NV>(y + i, yv[u]);
+        load_values<NV>(dy + i, dv[u]);
     }
-    float m[NV], is[NV], ga[NV], db[NV], dg[NV];
+    float f[5][NV];
+    bn_factors<KIND, 5>(l, C, {mean, inv_std, gamma, dbeta, dgamma}, f);
+    if (!l.active) return;
 #pragma unroll
-    for (int e = 0; e < NV; ++e) {
-        const int c = l.channel(e, C);
-        m[e] = mean[c];
-        is[e] = inv_std[c];
-        ga[e] = gamma[c];
-        db[e] = dbeta[c];
-        dg[e] = dgamma[c];
-    }
-#pragma unroll
-    for (int u = 0; u < kBnRows; ++u) {
+    for (int u = 0; u < ROWS; ++u) {
         if (r + u * l.tpr >= srows) break;
         uint16_t* const o = dx + (r + u * l.tpr) * l.width + l.col;
         float v[NV];
 #pragma unroll
-        for (int e = 0; e < NV; ++e) v[e] = grad(xv[u][e], yv[u][e], dv[u][e], m[e], is[e], ga[e], db[e], dg[e]);
+        for (int e = 0; e < NV; ++e)
+            v[e] = grad(xv[u][e], yv[u][e], dv[u][e], f[0][e], f[1][e], f[2][e], f[3][e], f[4][e]);
         if constexpr (NV == 8)
             *reinterpret_cast<u32x4*>(o) = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
                                                  pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
@@ -888,10 +922,11 @@ hipError_t launch_avgpool(int32_t N, int32_t HW, int32_t C, const uint16_t* x, v
     return hipGetLastError();
 }
 
-// FLAT from this many values on: its 16-byte loads win by size (4.3 M values of 31 channels:
-// 16.5 and 21.9 us forward and backward, 20.5 and 30.6 one value at a time; 81 M of 226: 231 and 280,
-// 410 and 568); below, its few blocks and longer LDS combination lose (1.9 M of 226: 18.0 and 20.3
-// against 13.5 and 16.0; 0.6 M of 17: 15.3 and 12.7 against 11.4 and 10.7).
+// FLAT from this many values on: its 16-byte loads win by size (sums of the three kernels, forward and
+// backward, us: 4.3 M values of 31 channels 16.2 and 19.7, one value at a time 17.6 and 20.3; 4.3 M of 226 16.7
+// and 21.0 against 19.7 and 22.6; 81 M of 226 102 and 209 against 207 and 299); below, its few blocks and longer
+// LDS combination lose (2.1 M of 226 equal, 14.4 and 16.5; 1.4 M 13.0 and 14.7 against 12.0 and 13.9; 0.6 M
+// of 17 12.8 and 13.7 against 10.3 and 11.0).
 constexpr int64_t kBnFlatMin = (int64_t)1 << 21;
 BnPlan plan_bn(int64_t rows, int32_t C) {
     BnPlan p;
@@ -908,21 +943,46 @@ BnPlan plan_bn(int64_t rows, int32_t C) {
     p.rpc = rpc;
     p.chunks = (srows + rpc - 1) / rpc;
     p.slices = (G + 255) / 256;
-    p.blocks = (srows + kBnRows * p.tpr - 1) / (kBnRows * p.tpr);
+    // Rows per thread of the element-wise passes: four where that leaves enough blocks, so that its factors serve
+    // more values, else one.  Measured forward / backward, us, with four and with one: 8 channels a thread, 392
+    // blocks of four rows (25088 x 128) 4.7 / 6.3 and 5.0 / 6.4, 196 (12544 x 128) 3.7 / 5.1 and 3.6 / 4.9, 98
+    // (12544 x 64) 3.6 / 4.6 and 3.0 / 3.5; one channel a thread, 1250 blocks (10000 x 100) 3.5 / 4.2 and 3.9 /
+    // 5.5, 560 (1117 x 260) 3.0 / 3.9 and 2.7 / 3.1.  FLAT always has them.
+    const int64_t blocks4 = (srows + 4 * p.tpr - 1) / (4 * p.tpr) * p.slices;
+    p.apply_rows = p.kind == BN_FLAT || blocks4 >= (p.kind == BN_VEC ? 256 : 768) ? 4 : 1;
+    p.blocks = (srows + p.apply_rows * p.tpr - 1) / (p.apply_rows * p.tpr);
     p.ws_bytes = (size_t)2 * p.chunks * C * 4;
     return p;
 }
 
 namespace {
 
-// f(kind) with the plan's kind as a compile-time constant
+// f(kind, rows) with the plan's kind and rows per thread of the element-wise passes as compile-time
+// constants, and g(lanes) with the finalize passes' chunk lanes
 template <typename F>
 void bn_dispatch(const BnPlan& p, F f) {
+    const auto with_rows = [&](auto kind) {
+        if (p.apply_rows == 1)
+            f(kind, std::integral_constant<int, 1>{});
+        else
+            f(kind, std::integral_constant<int, 4>{});
+    };
     switch (p.kind) {
-        case BN_VEC: f(std::integral_constant<int, BN_VEC>{}); break;
-        case BN_FLAT: f(std::integral_constant<int, BN_FLAT>{}); break;
-        default: f(std::integral_constant<int, BN_SCALAR>{}); break;
+        case BN_VEC: with_rows(std::integral_constant<int, BN_VEC>{}); break;
+        case BN_FLAT: with_rows(std::integral_constant<int, BN_FLAT>{}); break;
+        default: with_rows(std::integral_constant<int, BN_SCALAR>{}); break;
     }
+}
+
+// 16 chunk lanes (256 threads) up to 208 chunks, 64 beyond (forward / backward, us, with 16 and with 64: 12 chunks
+// of 64 channels 2.4 / 1.9 and 2.6 / 2.2, 196 of 128 3.2 / 3.0 and 4.1 / 3.2, 250 of 250 4.8 / 4.7 and 4.0 / 3.2, 512
+// of 128 4.8 / 4.7 and 3.9 / 3.9).
+template <typename G>
+void bn_lanes(const BnPlan& p, G g) {
+    if (p.chunks <= 208)
+        g(std::integral_constant<int, 16>{});
+    else
+        g(std::integral_constant<int, 64>{});
 }
 
 }  // namespace
@@ -937,13 +997,17 @@ hipError_t launch_bn_train_fwd(const uint16_t* x, int64_t rows, int32_t C, const
     const unsigned cb = (unsigned)((C + 15) / 16);
     const uint16_t* none = nullptr;
     const float* nof = nullptr;
-    bn_dispatch(p, [&](auto kind) {
+    bn_dispatch(p, [&](auto kind, auto per_thread) {
+        constexpr int KIND = decltype(kind)::value, ROWS = decltype(per_thread)::value;
         // one pass over x for both statistics (shifted sums), then the per-channel finalize
-        hipLaunchKernelGGL((bn_partial_kernel<BN_STATS, decltype(kind)::value>), dim3((unsigned)p.chunks, (unsigned)p.slices),
+        hipLaunchKernelGGL((bn_partial_kernel<BN_STATS, KIND>), dim3((unsigned)p.chunks, (unsigned)p.slices),
                            dim3(256), 0, s, x, none, none, rows, C, p.rpc, 0, nof, nof, p1, p2);
-        hipLaunchKernelGGL(bn_stats_finalize_kernel, dim3(cb), dim3(1024), 0, s, p1, p2, p.chunks, C, rows, eps, x, mean,
-                           inv_std);
-        hipLaunchKernelGGL((bn_apply_kernel<decltype(kind)::value>), dim3((unsigned)p.blocks, (unsigned)p.slices), dim3(256),
+        bn_lanes(p, [&](auto lanes) {
+            constexpr int L = decltype(lanes)::value;
+            hipLaunchKernelGGL(bn_stats_finalize_kernel<L>, dim3(cb), dim3(16 * L), 0, s, p1, p2, p.chunks, C, rows, eps, x,
+                               mean, inv_std);
+        });
+        hipLaunchKernelGGL((bn_apply_kernel<KIND, ROWS>), dim3((unsigned)p.blocks, (unsigned)p.slices), dim3(256),
                            0, s, x, rows, C, mean, inv_std, gamma, beta, relu, y);
     });
     return hipGetLastError();
@@ -956,12 +1020,16 @@ hipError_t launch_bn_train_bwd(const uint16_t* x, const uint16_t* y, const uint1
     if (p.blocks > 0x7FFFFFFF || p.chunks > 0x7FFFFFFF || p.slices > 65535) return hipErrorInvalidValue;
     float* p1 = ws;
     float* p2 = ws + p.chunks * C;
-    bn_dispatch(p, [&](auto kind) {
-        hipLaunchKernelGGL((bn_partial_kernel<BN_BWD, decltype(kind)::value>), dim3((unsigned)p.chunks, (unsigned)p.slices),
+    bn_dispatch(p, [&](auto kind, auto per_thread) {
+        constexpr int KIND = decltype(kind)::value, ROWS = decltype(per_thread)::value;
+        hipLaunchKernelGGL((bn_partial_kernel<BN_BWD, KIND>), dim3((unsigned)p.chunks, (unsigned)p.slices),
                            dim3(256), 0, s, x, y, dy, rows, C, p.rpc, relu, mean, inv_std, p1, p2);
-        hipLaunchKernelGGL(bn_bwd_finalize_kernel, dim3((unsigned)((C + 15) / 16)), dim3(1024), 0, s, p1, p2, p.chunks, C,
-                           dbeta, dgamma);
-        hipLaunchKernelGGL((bn_bwd_apply_kernel<decltype(kind)::value>), dim3((unsigned)p.blocks, (unsigned)p.slices),
+        bn_lanes(p, [&](auto lanes) {
+            constexpr int L = decltype(lanes)::value;
+            hipLaunchKernelGGL(bn_bwd_finalize_kernel<L>, dim3((unsigned)((C + 15) / 16)), dim3(16 * L), 0, s, p1, p2, p.chunks,
+                               C, dbeta, dgamma);
+        });
+        hipLaunchKernelGGL((bn_bwd_apply_kernel<KIND, ROWS>), dim3((unsigned)p.blocks, (unsigned)p.slices),
                            dim3(256), 0, s, x, y, dy, rows, C, relu, mean, inv_std, gamma, dgamma, dbeta, dx);
     });
     return hipGetLastError();

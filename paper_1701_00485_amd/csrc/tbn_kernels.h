@@ -331,6 +331,7 @@ struct BnPlan {
     int64_t blocks;       // of the element-wise passes
     int32_t slices;       // groups of 256 channel groups
     int32_t tpr;          // rows a block covers at a time
+    int32_t apply_rows;   // rows per thread of the element-wise passes
     int32_t kind;         // 8 channels per thread, 8 values over uneven channels, or one channel
     size_t ws_bytes;      // two fp32 partial arrays [chunks][C]
 };

@@ -20,8 +20,21 @@ def _close(got, want, tol):
 
 
 @pytest.mark.parametrize("c", [1, 3, 7, 8, 19, 24, 100, 255, 256, 257, 2056])
-@pytest.mark.parametrize("rows", [2, 7, 8, 9, 15, 64, 333, 2051])
+@pytest.mark.parametrize("rows", [1, 2, 7, 8, 9, 15, 64, 333, 2051])
 def test_batchnorm_layouts(tbn, rows, c):
+    _layout(tbn, rows, c)
+
+
+# the element-wise passes with one row and with four rows a thread (8 channels a thread: from 256 blocks of four on,
+# one channel: from 768), the finalize with 16 and with 64 chunk lanes (from 209 chunks on), each with a last
+# block that is partial
+@pytest.mark.parametrize("rows,c", [(32640, 64), (32641, 64), (40000, 19), (39870, 19), (1021, 1024), (3333, 1024),
+                                    (1999, 300), (1661, 1032), (1672, 1032)])
+def test_batchnorm_rules(tbn, rows, c):
+    _layout(tbn, rows, c)
+
+
+def _layout(tbn, rows, c):
     log("batch normalisation %d x %d" % (rows, c))
     g = torch.Generator(device="cuda").manual_seed(rows * 4099 + c)
     x = (torch.randn(rows, c, generator=g, device="cuda") + torch.randn(c, generator=g, device="cuda")).bfloat16()
