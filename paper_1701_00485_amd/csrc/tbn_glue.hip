@@ -889,9 +889,13 @@ hipError_t launch_maxpool_bwd(const PoolArgs& a, const uint16_t* dy, const int32
     const int64_t total = (int64_t)a.N * a.H * a.W * a.C;
     const int64_t out_total = (int64_t)a.N * a.P * a.Q * a.C;
     const int64_t cp = ((int64_t)a.H + a.k - 1) / a.k, cq = ((int64_t)a.W + a.k - 1) / a.k;
+    const int64_t cells = a.N * cp * cq * (a.C / 8);
+    // by cells from 32768 threads on (k = 2 / 3, of the gather's time: 32 k to 48 k threads 0.91 / 0.96, 100 k to
+    // 150 k 0.76 / 0.71); below, its k x k stores one after the other are a longer chain than the gather's
+    // two loads (16 k to 32 k 1.02 / 1.10, below 16 k 1.05 / 1.30)
     if (a.C % 8 == 0 && a.k == a.s && a.pad == 0 && (a.k == 2 || a.k == 3) && total < 0x7FFFFFFFll &&
-        a.N * cp * cq * (a.C / 8) < 0x7FFFFFFFll) {
-        const uint32_t groups = (uint32_t)(a.N * cp * cq * (a.C / 8));
+        cells >= 32768 && cells < 0x7FFFFFFFll) {
+        const uint32_t groups = (uint32_t)cells;
         const FastDiv dg = make_fastdiv((uint32_t)(a.C / 8)), dq = make_fastdiv((uint32_t)cq),
                       dp = make_fastdiv((uint32_t)cp);
         if (a.k == 2)

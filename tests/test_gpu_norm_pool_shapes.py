@@ -1,7 +1,8 @@
 """Batch normalisation at row and channel counts around its thread layouts (8 channels per thread, 8
 values over uneven channel counts with every remainder of rows against 8, one channel per thread; one
 row, chunks with remainders of the unrolled steps, several slices of channels), and pooling backward over
-windows that do not overlap, with input rows and columns past the last window.  Against fp64 torch:
+windows that do not overlap, with input rows and columns past the last window, on both sides of the size from
+which windows and not inputs are walked.  Against fp64 torch:
 the layers' bf16 outputs differ by their rounding (half a unit of bf16, 2^-9 of a value, plus fp32 sums:
 6e-3 of the largest value), the per-channel fp32 results by fp32 sums (1e-5).
 """
@@ -87,7 +88,8 @@ def test_batchnorm_uneven_channels_of_a_large_tensor(tbn, c):
 
 
 @pytest.mark.parametrize("k", [2, 3])
-@pytest.mark.parametrize("n,h,w,c", [(1, 2, 3, 8), (2, 7, 5, 16), (3, 9, 9, 24), (1, 4, 8, 40), (2, 6, 11, 5)])
+@pytest.mark.parametrize("n,h,w,c", [(1, 2, 3, 8), (2, 7, 5, 16), (3, 9, 9, 24), (1, 4, 8, 40), (2, 6, 11, 5),
+                                     (2, 126, 128, 32), (2, 127, 129, 32), (3, 115, 117, 56), (3, 115, 121, 56)])
 def test_maxpool_backward_cells(tbn, k, n, h, w, c):
     if min(h, w) < k:
         pytest.skip("window larger than the input")
