@@ -80,14 +80,9 @@ int wgrad_splits(const Geometry& g) {
     const int64_t chunks = (g.N * g.P * g.Q + 63) / 64;
     const int64_t target = dma ? plan.resident_blocks : 1024;
     int64_t splits = target / tiles;
-    // chunks per split at least: 16 for the 256 x 256 kernel, 4 for the register-staged one (its
-    // first-layer shapes have one output tile and a long reduction).  The narrow kernel's blocks
-    // take a split's chunks two at a time: small gradients (whose partials cost little) go down to
-    // 2, measured 8.1 against 18.3 us with 16 for 13 x 13 x 296 -> 8 at batch 9 and 10.8 against
-    // 18.8 us for 13 x 13 x 8 -> 120 at batch 90; larger ones stop at 8 (28 x 28 x 128 -> 128, 3 x 3,
-    // batch 64: 36.3 us with 8, 38.3 with 1).
-    const bool small = g.K * J < 65536;
-    const int64_t min_chunks = !dma ? 4 : plan.cfg == 1 ? 16 : small ? 2 : 8;
+    // chunks per split at least: the kernel's own, 4 for the register-staged one (its first-layer
+    // shapes have one output tile and a long reduction)
+    const int64_t min_chunks = dma ? plan.min_chunks : 4;
     const int64_t max_by_len = chunks / min_chunks > 0 ? chunks / min_chunks : 1;
     if (splits > max_by_len) splits = max_by_len;
     if (splits > 256) splits = 256;

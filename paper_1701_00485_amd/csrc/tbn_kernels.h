@@ -198,6 +198,7 @@ struct WgradDmaPlan {
     int cfg, tiles, resident_blocks;
     int tk, tj;  // filters x columns of a block tile
     int pix;     // 256 x 256 kernel: pixels per stage (32, 48 or 64)
+    int min_chunks;  // 64-pixel chunks per split at least
 };
 WgradDmaPlan wgrad_dma_plan(const WgradArgs& a);
 hipError_t launch_wgrad_dma(const WgradArgs& a, hipStream_t stream);

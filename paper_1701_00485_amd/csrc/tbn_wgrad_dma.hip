@@ -744,24 +744,63 @@ bool wgrad_dma_eligible(const WgradArgs& a) {
 WgradDmaPlan wgrad_dma_plan(const WgradArgs& a) {
     WgradDmaPlan p;
     const int K = a.K, J = a.R * a.S * a.C;
+    const int64_t chunks = ((int64_t)a.N * a.P * a.Q + 63) / 64;
     const int forced = knob(KNOB_WGRAD_CFG);
     const bool narrow_ok = a.H + a.ph <= 32767 && a.W + a.pw <= 32767 && a.ph <= 32767 && a.pw <= 32767;
-    p.tk = p.tj = 256;
+    // A tile and what follows from it (output tiles, least chunks of a split); returns the blocks and, by way of
+    // `us`, an estimate of its time for tiles of 256 columns: launch, rounds of 256 blocks of (epilogue + chunks),
+    // and the reduction of the partials.
+    auto take = [&](int tk, int tj, double* us) {
+        p.tk = tk;
+        p.tj = tj;
+        p.cfg = tk == 256 && tj == 256 ? 1 : 0;
+        p.tiles = ((K + tk - 1) / tk) * ((J + tj - 1) / tj);
+        // The narrow kernel's blocks take a split's chunks two at a time: small gradients (whose partials
+        // cost little) go down to 2, measured 8.1 against 18.3 us with 16 for 13 x 13 x 296 -> 8 at batch 9
+        // and 10.8 against 18.8 us for 13 x 13 x 8 -> 120 at batch 90; larger ones stop at 8 (28 x 28 x 128 ->
+        // 128, 3 x 3, batch 64: 36.3 us with 8, 38.3 with 1)
+        p.min_chunks = p.cfg == 1 ? 16 : (int64_t)K * J < 65536 ? 2 : 8;
+        const int64_t by_len = chunks / p.min_chunks > 1 ? chunks / p.min_chunks : 1;
+        const int64_t by_cus = 256 / p.tiles > 1 ? 256 / p.tiles : 1;
+        const int64_t splits = by_len < by_cus ? by_len : by_cus;
+        const double epilogue = tk == 32 ? 2.3 : tk == 64 ? 4.2 : tk == 128 ? 8.5 : 7.7;
+        const double chunk = tk == 32 ? 0.58 : tk == 64 ? 0.67 : tk == 128 ? 0.92 : 1.27;
+        const double partials = splits > 1 ? 2.5 + (double)(splits + 1) * K * J * 4 / 4.2e6 : 0.0;
+        const double block = epilogue + chunk * (double)((chunks + splits - 1) / splits);
+        *us = 3.0 + (double)((p.tiles * splits + 255) / 256) * block + partials;
+        return p.tiles * splits;
+    };
     // Narrow tiles up to 128 filters or 64 columns, against 256 x 256 ones (graph-replayed, with the
     // reduction of the partials): 32 x 32 x 128 -> 128 3 x 3 at batch 128 60 against 76 us, 56 x 56 x 64
     // -> 64 at batch 64 43 / 65, 36 x 39 x 384 -> 24 at batch 135 114 / 224, 1 x 1 8 -> 354 over 127 k
     // pixels 57 / 70; the segment-major kernel they replace (64-pixel stages, one 16-byte piece of 64
     // different rows per copy) took 80, 74, 276 and 83 us.
+    double us, best;
     if (narrow_ok && (forced == 0 || (forced != 1 && (K <= 128 || J <= 64)))) {
-        if (J <= 64) {
-            p.tj = 64;
-            p.tk = K <= 64 ? 64 : 256;
-        } else {
-            p.tk = K <= 32 ? 32 : K <= 64 ? 64 : 128;
+        if (J > 64)
+            take(K <= 32 ? 32 : K <= 64 ? 64 : 128, 256, &us);
+        else if (take(K <= 64 ? 64 : 256, 64, &us) < 192 && forced < 0)
+            take(64, 64, &us);  // few blocks of 256 filters: four times as many
+    } else {
+        take(256, 256, &us);
+    }
+    // Short reductions leave a large tile's blocks few, and most of their time is the epilogue: tiles of fewer
+    // filters where the estimate gains 7%.  Its constants are fitted to 15 layers (64 to 1024 filters, 512 to
+    // 13600 columns) over 49 to 12800 pixels with all four tiles; there its choice is on average 0.2% slower than
+    // the best tile and never more than 3.4% slower than the largest (400 -> 136 3 x 3 over 1568 pixels: 15.2 / 17.6 / 23.9 / 41.6 us
+    // with 32 / 64 / 128 / 256 filters; 256 -> 512 5 x 5 over 3200: 69.8 / 43.5 / 47.7 / 44.3).
+    best = us;
+    int tile = p.tk;
+    const int largest = p.tk;
+    for (int tk = largest / 2; forced < 0 && narrow_ok && p.tj == 256 && tk >= 32; tk /= 2) {
+        double t;
+        take(tk, 256, &t);
+        if (t < 0.93 * us && t < best) {
+            best = t;
+            tile = tk;
         }
     }
-    p.cfg = p.tk == 256 && p.tj == 256 ? 1 : 0;
-    p.tiles = ((K + p.tk - 1) / p.tk) * ((J + p.tj - 1) / p.tj);
+    if (p.tj == 256) take(tile, 256, &us);
     p.resident_blocks = 256;  // one block per CU
     // wide kernel: 48-pixel stages in a three-deep ring (measured best of 32 / 48 / 64)
     p.pix = 48;
