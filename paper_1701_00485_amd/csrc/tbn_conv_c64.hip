@@ -2,7 +2,7 @@
 // backward-data, Sec. 3) for 3 x 3 layers of stride 1 over 64 channels with many output pixels.  Their
 // reduction is short (nine 64-element stages), so on the tiled kernel every tile decodes its filters
 // again, copies every input pixel nine times, waits at nine barriers, and multiplies little per
-// decoded word: 56 x 56 x 64 -> 64 at batch 64 takes 28 us against the 7 us of its matrix work.
+// decoded word: 56 x 56 x 64 -> 64 at batch 64 takes 26.8 us against the 7 us of its matrix work.
 //
 //   * a wave keeps 32 decoded filters in registers (36 operands of 4 registers) for as long as it
 //     lives, so nothing is decoded in the loop;
@@ -288,6 +288,11 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args ka) {
 // against 21.6).  Fewer items belong to the small-layer kernel or were not faster; maps whose units
 // lie more than 0.4 past the edges waste more than the difference (at 0.31, 7 x 7 and 14 x 14,
 // 8.4 -> 7.7 and equal).
+// A wave's range is whole units, so the time goes by rounds of 2048 waves, of which edges and the last round fill
+// only a part with pixels.  Of the tiled kernel's time (600 random layers) by that share: 33 to 64 filters, two
+// rounds 1.02-1.14 up to 0.48, 0.79-0.96 above; three 1.04-1.09 up to 0.65, 0.79-0.97 above; four and more 1.02-1.09
+// up to 0.73, 0.67-0.99 above; 128 filters 1.03-1.10 up to 0.78, 0.81-1.01 above.  Up to 32 and at 96 filters
+// below 0.94 at every share, as the tiles are half empty there.
 bool conv_c64_chosen(const ConvGemmArgs& a, int cfg) {
     if (cfg != 60 && (cfg >= 0 || conv_splits_override() > 0)) return false;
     if (a.C != C64 || a.R != 3 || a.S != 3 || a.sh != 1 || a.sw != 1 || a.y_f32 || a.Kf % 8 != 0) return false;
@@ -296,7 +301,12 @@ bool conv_c64_chosen(const ConvGemmArgs& a, int cfg) {
     const int64_t units = (int64_t)a.N * ((a.P + UP - 1) / UP) * ((a.Q + UQ - 1) / UQ);
     if (cfg == 60) return true;
     const int64_t items = units * ((a.Kf + 31) / 32);
-    return a.Kf <= 128 && items >= (a.Kf == 128 ? 8192 : 1024) && units * (UP * UQ) * 5 <= M * 7;
+    if (a.Kf > 128 || items < (a.Kf == 128 ? 8192 : 1024) || units * (UP * UQ) * 5 > M * 7) return false;
+    const int64_t fgroups = (a.Kf + 31) / 32, per = (items < 2048 ? items : 2048) / fgroups;
+    const int64_t rounds = (units + per - 1) / per, slots = rounds * per * (UP * UQ);
+    if (a.Kf == 128) return M * 100 > slots * 78;
+    // more pixels than the rounds but the last could hold, or nearly three quarters of all
+    return a.Kf <= 32 || a.Kf > 64 || M * rounds >= slots * (rounds - 1) || M * 100 >= slots * 74;
 }
 
 hipError_t launch_conv_c64(const ConvGemmArgs& g, hipStream_t stream) {

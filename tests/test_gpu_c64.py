@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 CASES = [(1, 1, 1, 8, 1), (1, 4, 8, 32, 1), (2, 5, 9, 40, 1), (3, 3, 7, 64, 1), (1, 12, 17, 72, 0), (2, 9, 6, 24, 2),
          (5, 13, 11, 200, 1)]
 # ... and on either side of the rule that chooses it
-RULE = [(9, 28, 28, 64, 1), (30, 28, 28, 64, 1), (21, 41, 38, 64, 1), (12, 56, 56, 64, 1), (40, 30, 31, 104, 1)]
+RULE = [(9, 28, 28, 64, 1), (30, 28, 28, 64, 1), (21, 41, 38, 64, 1), (12, 56, 56, 64, 1), (40, 30, 31, 104, 1),
+        (48, 26, 26, 64, 1), (50, 26, 26, 64, 1)]
 
 
 def _check(tbn, case, knobs, forced):
