@@ -36,8 +36,8 @@ typedef enum tbn_knob {
     TBN_KNOB_WGRAD_PIX = 3,
     /* weight gradient: L2 prefetch this many stages ahead (0 = off) */
     TBN_KNOB_WGRAD_PF = 4,
-    /* int8-activation forward tile: 1 128x256, 2 128x128, 3 128x64, 4 64x128, 5-8 small-layer kernel
-     * (filters per tile, waves) = (32, 4) (32, 8) (32, 16) (64, 8) */
+    /* int8-activation forward tile: 1 128x256, 2 128x128, 3 128x64, 4 64x128, 5-7 small-layer kernel
+     * (filters per tile, waves) = (32, 4) (32, 8) (64, 8) */
     TBN_KNOB_I8_TILE = 5,
     /* weight-streaming forward: 0-7 select (16-byte code loads per buffer, buffers in flight
      * per wave, groups of four waves per block) = (2,4,1) (4,2,1) (8,2,1) (4,3,1) (2,4,2)

@@ -453,7 +453,7 @@ bool conv_fp8_eligible(const ConvFp8Args& a) {
 
 int conv_fp8_tile(const ConvFp8Args& a) {
     const int forced = knob(KNOB_FP8_TILE);
-    if (forced >= 1 && forced <= 8) return forced;
+    if (forced >= 1 && forced <= 7) return forced;
     return conv_code8_tile(a.N, a.P, a.Q, a.K, (int64_t)a.R * a.S * a.C);
 }
 

@@ -441,7 +441,7 @@ bool conv_i8_eligible(const ConvI8Args& a) {
 
 int conv_i8_tile(const ConvI8Args& a) {
     const int forced = knob(KNOB_I8_TILE);
-    if (forced >= 1 && forced <= 8) return forced;
+    if (forced >= 1 && forced <= 7) return forced;
     return conv_code8_tile(a.N, a.P, a.Q, a.K, (int64_t)a.R * a.S * a.C);
 }
 

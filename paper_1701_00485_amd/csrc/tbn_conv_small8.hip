@@ -294,7 +294,6 @@ hipError_t launch_small8(const Args& g, int cfg, hipStream_t stream) {
     switch (cfg) {
         case 5: return launch_cfg<FP8, 1, 4, 3>(a, stream);
         case 6: return launch_cfg<FP8, 1, 8, 3>(a, stream);
-        case 7: return launch_cfg<FP8, 1, 16, 1>(a, stream);
         default: return launch_cfg<FP8, 2, 8, 3>(a, stream);
     }
 }
@@ -311,7 +310,7 @@ int conv_code8_tile(int32_t N, int32_t P, int32_t Q, int32_t K, int64_t n) {
     const int64_t rows = (M + 31) / 32, b1 = rows * ((K + 31) / 32), b2 = rows * ((K + 63) / 64);
     const int64_t nst = (n + 127) / 128;
     if (b1 <= 256) return nst <= 8 ? 5 : 6;
-    if (b1 <= 512) return nst >= 12 && b2 <= 256 ? 8 : 5;
+    if (b1 <= 512) return nst >= 12 && b2 <= 256 ? 7 : 5;
     int cfg = K > 128 ? 1 : (K > 64 ? 2 : 3);
     const int bm = 128, bn = cfg == 1 ? 256 : (cfg == 2 ? 128 : 64);
     // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles beyond 64 filters.  Measured at

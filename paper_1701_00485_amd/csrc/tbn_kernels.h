@@ -269,7 +269,7 @@ struct ConvI8Args {
 };
 bool conv_i8_eligible(const ConvI8Args& a);
 // Tile shape (1: 128 x 256, 2: 128 x 128, 3: 128 x 64, 4: 64 x 128, small-layer kernel with filters
-// per tile and waves 5: 32, 4, 6: 32, 8, 7: 32, 16, 8: 64, 8); the int8 tile knob forces one.
+// per tile and waves 5: 32, 4, 6: 32, 8, 7: 64, 8); the int8 tile knob forces one.
 int conv_i8_tile(const ConvI8Args& a);
 hipError_t launch_conv_i8(const ConvI8Args& a, hipStream_t stream);
 // The built-in choice for K filters of n elements, either format.

@@ -26,7 +26,7 @@ RULE = [(1, 131, 129, 16, 64, 1, 1, 1, 0), (1, 131, 129, 16, 65, 1, 1, 1, 0), (1
         (1, 222, 223, 16, 64, 1, 1, 1, 0), (1, 222, 223, 16, 65, 1, 1, 1, 0)]
 
 
-@pytest.mark.parametrize("tile", [-1, 5, 6, 7, 8])
+@pytest.mark.parametrize("tile", [-1, 5, 6, 7])
 def test_small_layers_8bit(tbn, tile, knobs):
     knobs(i8_tile=tile, fp8_tile=tile)
     for g in CASES + (RULE if tile < 0 else []):
