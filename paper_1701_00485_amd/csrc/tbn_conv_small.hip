@@ -292,14 +292,18 @@ hipError_t launch_cfg(const SmallArgs& args, hipStream_t stream) {
 // are the blocks with tiles of 32 and 64 filters):
 //   b1 <= 256 (a block per CU): 56 x 56 x 64 at batch 1 7.3 -> 4.7, 28 x 28 x 128 9.0 -> 5.0, 14 x 14 x 256
 //     12.5 -> 5.9, 7 x 7 x 512 12.6 -> 7.8, 64 rows of 512 -> 1000 8.4 -> 4.3, 128 rows of 8192 -> 10 12.5 ->
-//     10.1.  Eight waves, four where eight would have a stage or less each, sixteen from 72 stages on.
+//     10.5.  Eight waves, four where eight would have a stage or less each, sixteen (whose rings hold one
+//     stage) from 72 stages on: 48 stages 7.1 with eight, 7.4 with sixteen, 64 to 90 equal, 126 (14 x 14 x 896)
+//     11.2 and 10.6, 200 14.2 and 12.5.
 //   b1 <= 512: four waves, two blocks per CU: 56 x 56 x 64 at batch 2 7.3 -> 5.4, 40 x 40 x 16 5 x 5 at
 //     batch 9 10.1 -> 5.0; from 24 stages on 64 filters and eight waves if that is at most a block
 //     per CU (7 x 7 x 512 at batch 16: 18.7 -> 10.8, against 12.0).
 //   b1 <= 1024: only where the tiled kernel splits its reduction over the grid (an epilogue pass of
 //     its own): 16 x 16 x 96 at batch 25 16.2 -> 8.8, 52 x 78 x 96 at batch 2 17.2 -> 8.8; otherwise the
 //     tiled kernel is as fast or faster (28 x 28 x 128 at batch 6 9.3 against 9.4, 56 x 56 x 64 at batch
-//     4 7.5 against 7.9).
+//     4 7.5 against 7.9).  Four waves, 64 filters a tile from 24 stages on: 14 stages (the two above) 9.2 with
+//     32 filters, 9.5 with 64, 24 (1 x 1 x 1536 -> 72) equal, 36 (14 x 14 x 256 -> 96 at batch 30) 12.8 and 12.4,
+//     128 (100 rows of 8192 -> 8000) 36.3 and 30.4.
 // Reductions beyond 200 stages stay on the tiled kernel, which spreads them over the grid.
 int conv_small_cfg(const ConvGemmArgs& a, int cfg) {
     if (cfg >= 51 && cfg <= 55) return cfg;

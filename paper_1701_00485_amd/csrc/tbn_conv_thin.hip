@@ -83,8 +83,8 @@ __device__ __forceinline__ uint32_t load_patch(const ConvGemmArgs& a, const uint
 
 // The zero-bordered copy of the input: xp[n][h'][w'][c] = x[n][h' - ph][w' - pw][c] inside
 // the image and for c < C, else 0 (bf16).  One thread per padded pixel, CP elements each; pixel
-// indices below 2^32 (the copy is below 2 GiB), split by multiply-shift divisions: 15.1 us with 64-bit
-// divisions, 12.2 us without (64 x 224 x 224 x 3).
+// indices below 2^30 (the copy is below 2 GiB, a pixel 2 bytes or more), split by multiply-shift divisions
+// (numerators below 2^31): 15.1 us with 64-bit divisions, 12.2 us without (64 x 224 x 224 x 3).
 template <int CP, bool X32>
 __global__ __launch_bounds__(256) void thin_pad_kernel(const ConvGemmArgs a, const ThinGeom g, uint16_t* xp) {
     const uint32_t total = (uint32_t)a.N * (uint32_t)g.Hp * (uint32_t)g.Wp;

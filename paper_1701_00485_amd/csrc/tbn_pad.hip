@@ -1,7 +1,7 @@
 // tbn_pad.hip -- what is prepared ahead of a GEMM: the codes of the transposed, flipped filters for
 // backward-data; and for channel counts that are no multiple of 8 the copies that bring such a layer
-// to the LDS-DMA kernels (16-byte pieces of 8 bf16 channels).  A tensor is copied into Cp channels, a multiple of 8, with zeros beyond the real
-// ones; a filter's two-bit codes are re-packed from rows of C to rows of Cp channels (the codes
+// to the LDS-DMA kernels (16-byte pieces of 8 bf16 channels).  A tensor is copied into Cp channels, a multiple
+// of 8, with zeros beyond the real ones; a filter's two-bit codes are re-packed from rows of C to rows of Cp channels (the codes
 // of the added channels multiply zeros, so they may be anything: their bits are clear).
 #include "tbn_device.h"
 #include "tbn_kernels.h"

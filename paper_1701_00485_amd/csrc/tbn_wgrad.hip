@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void split_reduce_vec4_kernel(const float* __r
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += v[u];
         }
-        // the rest together: past the end re-read the last split and add nothing
+        // the rest together; past the end nothing is loaded or added
         f32x4 v[7];
 #pragma unroll
         for (int u = 0; u < 7; ++u)
@@ -307,7 +307,10 @@ template <bool COMPACT>
 hipError_t launch_vec4(const float* part, int32_t splits, int64_t count4, int64_t stride, int32_t C, int32_t Cp,
                        float* dw, int32_t accumulate, hipStream_t stream) {
     const FastDiv div_cp = make_fastdiv((uint32_t)Cp);
-    // enough threads to fill the chip, at least two splits each
+    // enough threads to fill the chip, at least two splits each.  Whole filter gradients with 1, 4 and 16 threads,
+    // us: 2304 groups of 128 splits 30.4 / 26.0 / 25.3; 4096 of 256 39.9 / 32.6 / 31.7; 9216 of 42 15.4 / 13.9 / 13.9;
+    // 18432 of 42 23.4 / 22.7 / 22.6; 36864 of 51 (32 x 32 x 128 -> 128 3 x 3 at batch 128) and 73728 of 32 equal (60.4,
+    // 42.0); 36864 of 6 13.6 / 13.7 / 14.6; 294912 of 7 40.8 / 40.5 / 45.1.
     const int G = count4 >= 65536 || splits < 8 ? 1 : count4 >= 16384 || splits < 32 ? 4 : 16;
     const dim3 grid((unsigned)((count4 * G + 255) / 256));
     if (G == 1)
