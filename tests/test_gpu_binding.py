@@ -1,6 +1,7 @@
 """The native marshalling of the Python calls: every call gives bit for bit what the ctypes code
 gives for the same arguments (allocated and caller-provided outputs, optional operands given and
-not), and what it declines raises what the ctypes code raises.
+not), and what it declines raises what the ctypes code raises.  That it answers the ordinary calls itself and
+declines the others is recorded: where it declined everything, both sides would run the ctypes code.
 """
 import pytest
 import torch
@@ -13,6 +14,9 @@ class _Declines:
 
     def __getattr__(self, name):
         return lambda *args: NotImplemented
+
+
+LIBRARY_REFUSES = ("small workspace", "misaligned", "stride")
 
 
 def _tensors(o):
@@ -67,6 +71,7 @@ def _calls(tbn):
         "bn bwd": lambda: tbn.batchnorm_train_bwd(x, a, x, mean, inv, gamma, relu=True, dgamma=torch.empty_like(gamma)),
         "relu bwd": lambda: tbn.relu_bwd(x, a),
         "xent": lambda: tbn.softmax_xent(logits, labels),
+    }, {
         # declined: the errors are those of the ctypes code
         "cpu tensor": lambda: tbn.relu_bwd(x.cpu(), x),
         "strided": lambda: tbn.conv2d_fwd(d, x.transpose(1, 2), codes, alpha),
@@ -81,8 +86,28 @@ def _calls(tbn):
     }
 
 
+class _Recorder:
+    """Passes calls on to the native module and notes which of them it declined."""
+
+    def __init__(self, module):
+        self.module, self.answered, self.declined = module, 0, 0
+
+    def __getattr__(self, name):
+        def call(*args):
+            try:
+                out = getattr(self.module, name)(*args)
+            except Exception:  # an error of the library: the call was taken
+                self.answered += 1
+                raise
+            self.declined += out is NotImplemented
+            self.answered += out is not NotImplemented
+            return out
+        return call
+
+
 def test_native_calls_equal_ctypes_calls(tbn, monkeypatch):
-    calls = _calls(tbn)
+    ordinary, refused = _calls(tbn)
+    monkeypatch.setattr(tbn, "_native", None)
 
     def outcome(f):
         try:
@@ -90,13 +115,21 @@ def test_native_calls_equal_ctypes_calls(tbn, monkeypatch):
         except Exception as e:  # the type and the message are compared
             return (type(e), str(e))
 
-    native = {k: outcome(f) for k, f in calls.items()}
+    native, module = {}, tbn._load_native()
+    for calls in (ordinary, refused):
+        for name, f in calls.items():
+            recorder = _Recorder(module)
+            monkeypatch.setattr(tbn, "_native", recorder)
+            native[name] = outcome(f)
+            took = (recorder.answered, recorder.declined)
+            # what the library itself refuses (alignment, workspace, stride) is still an ordinary call to the binding
+            assert took == ((1, 0) if calls is ordinary or name in LIBRARY_REFUSES else (0, 1)), (name, took)
     monkeypatch.setattr(tbn, "_native", _Declines())
-    for name, f in calls.items():
+    for name, f in list(ordinary.items()) + list(refused.items()):
         print(name, flush=True)
         got, want = native[name], outcome(f)
-        if isinstance(want, tuple):
-            assert got == want
+        if name in refused:
+            assert isinstance(want, tuple) and got == want
             continue
         assert not isinstance(got, tuple), got
         assert [(t.shape, t.dtype) for t in got] == [(t.shape, t.dtype) for t in want]
