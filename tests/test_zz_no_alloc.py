@@ -19,12 +19,15 @@ def _bits(t):
 
 
 CASES = [
-    # (geometry, epilogue) -- each needs workspace under the default plan (batch-1 layers
-    # whose reduction is too long for the in-block wave groups split it over the grid)
+    # (geometry, epilogue) -- each asks for workspace under the default plan (the layers whose tiled
+    # plan splits the reduction over the grid; up to 200 stages of it the small-layer kernel runs
+    # them and leaves the workspace alone)
     ((1, 7, 7, 512, 512, 3, 3, 1, 1), True),      # ResNet-18 layer-4 shape at batch 1
     ((1, 5, 5, 384, 512, 3, 3, 1, 1), True),      # a smaller input, 54 stages
     ((8, 224, 224, 3, 64, 7, 7, 2, 3), False),    # the stem at batch 8 (bordered input copy)
     ((1, 7, 7, 512, 256, 3, 3, 1, 1), False),     # layer-4 input, 256 filters: smaller than the stem
+    ((1, 7, 7, 1536, 256, 3, 3, 1, 1), True),     # 216 stages: split over the grid, its sums in the scratch
+    ((1, 5, 5, 1536, 264, 3, 3, 1, 1), False),    # ... and a smaller input
 ]
 
 
