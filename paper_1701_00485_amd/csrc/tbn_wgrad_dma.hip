@@ -775,32 +775,41 @@ WgradDmaPlan wgrad_dma_plan(const WgradArgs& a) {
     // -> 64 at batch 64 43 / 65, 36 x 39 x 384 -> 24 at batch 135 114 / 224, 1 x 1 8 -> 354 over 127 k
     // pixels 57 / 70; the segment-major kernel they replace (64-pixel stages, one 16-byte piece of 64
     // different rows per copy) took 80, 74, 276 and 83 us.
-    double us, best;
-    if (narrow_ok && (forced == 0 || (forced != 1 && (K <= 128 || J <= 64)))) {
-        if (J > 64)
-            take(K <= 32 ? 32 : K <= 64 ? 64 : 128, 256, &us);
-        else if (take(K <= 64 ? 64 : 256, 64, &us) < 192 && forced < 0)
-            take(64, 64, &us);  // few blocks of 256 filters: four times as many
-    } else {
-        take(256, 256, &us);
-    }
-    // Short reductions leave a large tile's blocks few, and most of their time is the epilogue: tiles of fewer
-    // filters where the estimate gains 7%.  Its constants are fitted to 15 layers (64 to 1024 filters, 512 to
-    // 13600 columns) over 49 to 12800 pixels with all four tiles; there its choice is on average 0.2% slower than
-    // the best tile and never more than 3.4% slower than the largest (400 -> 136 3 x 3 over 1568 pixels: 15.2 / 17.6 / 23.9 / 41.6 us
-    // with 32 / 64 / 128 / 256 filters; 256 -> 512 5 x 5 over 3200: 69.8 / 43.5 / 47.7 / 44.3).
-    best = us;
-    int tile = p.tk;
-    const int largest = p.tk;
-    for (int tk = largest / 2; forced < 0 && narrow_ok && p.tj == 256 && tk >= 32; tk /= 2) {
-        double t;
-        take(tk, 256, &t);
-        if (t < 0.93 * us && t < best) {
-            best = t;
-            tile = tk;
+    double us;
+    int64_t blocks;
+    if (!narrow_ok || forced == 1 || (forced < 0 && K > 128 && J > 64))
+        blocks = take(256, 256, &us);
+    else if (J > 64)
+        blocks = take(K <= 32 ? 32 : K <= 64 ? 64 : 128, 256, &us);
+    else
+        blocks = take(K <= 64 ? 64 : 256, 64, &us);
+    // Short reductions leave a large tile's blocks few, and most of their time is the epilogue.  Below 192 blocks:
+    // 64 filters for 256 x 64; of 256-column tiles the one with the least estimate if that gains 7%.  The
+    // constants are fitted to 15 layers (64 to 1024 filters, 512 to 13600 columns) over 49 to 12800 pixels with all
+    // four tiles; there the least estimate is on average 0.2% slower than the best tile and the choice never more than
+    // 3.4% slower than the largest (400 -> 136 3 x 3 over 1568 pixels: 15.2 / 17.6 / 23.9 / 41.6 us with 32 / 64 /
+    // 128 / 256 filters; 256 -> 512 5 x 5 over 3200: 69.8 / 43.5 / 47.7 / 44.3).
+    // From 192 blocks on the large tile stays.  40 -> 104 3 x 3 over 25650 pixels, 256 blocks, would take 23.6 / 18.8 /
+    // 17.2 us with 128 / 64 / 32 by itself; but in a training iteration, with the workspace left to torch's
+    // allocator, the smaller workspace shares cached blocks with the other calls' buffers: 68.8 us the iteration
+    // with 128, 64.2 to 72.8 with 64, 73.5 with 32.
+    if (forced < 0 && narrow_ok && blocks < 192) {
+        if (p.tj == 64) {
+            take(64, 64, &us);
+        } else {
+            const int largest = p.tk;
+            int tile = largest;
+            double best = 0.93 * us, t;
+            for (int tk = largest / 2; tk >= 32; tk /= 2) {
+                take(tk, 256, &t);
+                if (t < best) {
+                    best = t;
+                    tile = tk;
+                }
+            }
+            take(tile, 256, &us);
         }
     }
-    if (p.tj == 256) take(tile, 256, &us);
     p.resident_blocks = 256;  // one block per CU
     // wide kernel: 48-pixel stages in a three-deep ring (measured best of 32 / 48 / 64)
     p.pix = 48;
