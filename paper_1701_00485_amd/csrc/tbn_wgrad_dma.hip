@@ -90,7 +90,7 @@ __device__ __forceinline__ void interleave_reads() {
 // and the next stage's first operands are read under that step's MFMAs.
 struct TapEntry {
     uint32_t off;  // byte offset of the pixel's (h0, w0, channel 0) in x, modulo 2^32
-    int32_t hw;    // h0 << 16 | w0 & 0xFFFF; h0 = -32768: not a pixel of this split
+    int32_t hw;    // h0 << 16 | w0 & 0xFFFF; h0 = -32768: not a pixel of this split (at no tap: R <= 32768)
 };
 
 template <int RS>
@@ -746,7 +746,8 @@ WgradDmaPlan wgrad_dma_plan(const WgradArgs& a) {
     const int K = a.K, J = a.R * a.S * a.C;
     const int64_t chunks = ((int64_t)a.N * a.P * a.Q + 63) / 64;
     const int forced = knob(KNOB_WGRAD_CFG);
-    const bool narrow_ok = a.H + a.ph <= 32767 && a.W + a.pw <= 32767 && a.ph <= 32767 && a.pw <= 32767;
+    // the table's 16-bit coordinates; a row of no pixel stays above the image at every tap
+    const bool narrow_ok = a.H + a.ph <= 32767 && a.W + a.pw <= 32767 && a.ph <= 32767 && a.pw <= 32767 && a.R <= 32768;
     // A tile and what follows from it (output tiles, least chunks of a split); returns the blocks and, by way of
     // `us`, an estimate of its time for tiles of 256 columns: launch, rounds of 256 blocks of (epilogue + chunks),
     // and the reduction of the partials.

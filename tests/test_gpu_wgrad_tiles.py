@@ -55,3 +55,22 @@ def _check(tbn, g, knobs, kernels):
         assert nerr(dw.cpu().numpy(), ref) <= 1e-4
         assert torch.equal(dw, again)
         assert nerr(twice.cpu().numpy(), 2 * ref) <= 1e-4
+
+
+def test_wgrad_window_of_more_than_32768_rows(tbn):
+    # 28 of the 32 rows of the only stage are no pixels: at tap 32768 they must not reach back into the
+    # images (x element 32768 * 8 on, infinite here), whatever dy they are multiplied with (zeros)
+    log("filter gradient, window of 33000 rows")
+    n, h, r, pad = 4, 10000, 33000, 11500
+    desc = tbn.ConvDesc(n, h, 1, 8, 8, r, 1, 1, pad, pad_w=0)
+    assert desc.out_dims() == (1, 1)
+    g = torch.Generator().manual_seed(3)
+    x, dy = torch.randn(n, h, 8, generator=g).bfloat16(), torch.randn(n, 8, generator=g).bfloat16()
+    flat = x.view(-1, 8)
+    flat[32768] = float("inf")  # row 2768 of image 3: tap 14268 sees it
+    want = torch.zeros(8, r, 8, dtype=torch.float64)
+    want[:, pad:pad + h] = torch.einsum("nk,nhc->khc", dy.double(), x.double())
+    got = tbn.conv2d_bwd_weight(desc, x.cuda(), dy.cuda()).cpu().double().view(8, r, 8)
+    hit = ~torch.isfinite(want)
+    assert torch.equal(~torch.isfinite(got), hit)
+    assert float((got - want)[~hit].abs().max()) <= 1e-4 * float(want[~hit].abs().max())
