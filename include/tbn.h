@@ -107,7 +107,9 @@ int64_t tbn_packed_bytes(int64_t k, int64_t n);
  * elements, a zero-bordered bf16 copy of the input with the channels padded to a power of
  * two (the forward call writes it first); the size covers either input dtype.  Channel counts
  * that are no multiple of 8 (C, and K in the backward passes) add a copy of the tensor with the
- * channels padded to one. */
+ * channels padded to one.  The partial sums are those of the tiled kernel's plan: a layer that
+ * another kernel runs without them asks for (and refuses less than) the same, so that a size
+ * does not depend on the kernel chosen or on the output type. */
 tbn_status tbn_workspace_size(tbn_op op, const tbn_conv_desc* desc, size_t* bytes);
 
 /*
