@@ -146,8 +146,14 @@ BwdDataWs bwd_data_ws(const Geometry& g) {
     w.apair_off = round_up(w.codes_bytes, 256);
     w.apair_bytes = nbt * 32 * 4;
     w.partial_off = w.apair_off + round_up(w.apair_bytes, 256);
-    // the split-K partials of the GEMM do not depend on the output dtype
-    w.partial_bytes = (int64_t)tbn::conv_gemm_partial_bytes(bwd_data_args(g, TBN_BF16));
+    // the split-K partials of the GEMM do not depend on the output dtype; at the launch it has scale pairs,
+    // which the weight-streaming kernel does not take: a layer that would go there without them may be split
+    tbn::ConvGemmArgs a = bwd_data_args(g, TBN_BF16);
+    w.partial_bytes = (int64_t)tbn::conv_gemm_partial_bytes(a);
+    static const uint32_t some_pairs = 0;
+    a.apair = &some_pairs;
+    const int64_t split = (int64_t)tbn::conv_gemm_split_bytes(a);
+    if (split > w.partial_bytes) w.partial_bytes = split;
     w.total = w.partial_off + w.partial_bytes;
     return w;
 }

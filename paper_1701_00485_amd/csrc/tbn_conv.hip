@@ -351,6 +351,13 @@ size_t conv_gemm_partial_bytes(const ConvGemmArgs& a) {
     }
 }
 
+size_t conv_gemm_split_bytes(const ConvGemmArgs& a) {
+    const int cfg = conv_tile_override();
+    FcStreamPlan fp;
+    ThinGeom tg;
+    return choose_path(a, cfg, &fp, &tg) == PATH_DMA ? plan_conv_dma(a, cfg).partial_bytes : 0;
+}
+
 bool conv_pool_plan(const ConvGemmArgs& a, ThinGeom* g) {
     FcStreamPlan fp;
     return choose_path(a, conv_tile_override(), &fp, g) == PATH_THIN && conv_thin_pool_plan(a, g);

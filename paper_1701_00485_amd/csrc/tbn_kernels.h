@@ -118,6 +118,8 @@ int conv_tile_override();
 int conv_splits_override();
 // Bytes of split-K partials the forward / backward-data GEMM of these arguments needs.
 size_t conv_gemm_partial_bytes(const ConvGemmArgs& a);
+// ... of which the kernel that runs them writes this many (apair: null or not, as at the launch).
+size_t conv_gemm_split_bytes(const ConvGemmArgs& a);
 // A forward layer that only the general kernel takes as it is because C % 8 != 0 (bf16 or fp32
 // input): copied and re-packed into workspace (total bytes) it runs on the LDS-DMA kernel.
 struct ConvPadPlan {

@@ -171,6 +171,14 @@ def test_workspace_sizes():
     assert tbn.workspace_size(tbn.OP_BWD_DATA, d) == codes_pairs
 
 
+def test_fully_connected_backward_workspace_holds_its_partials():
+    # one row, 16384 filters: forward such a window goes to the weight-streaming kernel, backward the reduction
+    # of 256 stages is split over the grid, with fp32 partials behind codes and scale pairs
+    d = tbn.ConvDesc(1, 1, 1, 1024, 16384, 1, 1, 1, 0)
+    rest = tbn.workspace_size(tbn.OP_BWD_DATA, d) - (16 * 256 * 1024 + 256 * 128)
+    assert rest > 0 and rest % (1024 * 4) == 0
+
+
 def test_stem_workspace_is_the_bordered_copy():
     # 7x7/2 stem over 64 x 224 x 224 x 3: 14 x 4 tiles of 8 x 32 outputs; the bordered copy
     # spans (14-1)*8*2 + 21 = 229 rows and (4-1)*32*2 + 70 = 262 columns of 4 channels

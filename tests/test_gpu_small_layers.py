@@ -64,3 +64,9 @@ def test_small_layer_shapes(tbn, tile, knobs):
 def test_small_layer_rule(tbn):
     for g in CASES + RULE:
         _check(tbn, g, "built-in choice")
+
+
+def test_one_row_backward_beyond_the_small_layers(tbn):
+    # a window as large as its input and 201 stages: backward-data of it is split over the grid
+    for g in [(1, 1, 1, 72, 12808, 1, 1, 1, 0), (1, 1, 1, 256, 16384, 1, 1, 1, 0), (1, 1, 1, 40, 3216, 2, 2, 1, 1)]:
+        _check(tbn, g, "one row")
