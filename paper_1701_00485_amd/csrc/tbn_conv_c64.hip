@@ -288,11 +288,15 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args ka) {
 // against 21.6).  Fewer items belong to the small-layer kernel or were not faster; maps whose units
 // lie more than 0.4 past the edges waste more than the difference (at 0.31, 7 x 7 and 14 x 14,
 // 8.4 -> 7.7 and equal).
-// A wave's range is whole units, so the time goes by rounds of 2048 waves, of which edges and the last round fill
-// only a part with pixels.  Of the tiled kernel's time (600 random layers) by that share: 33 to 64 filters, two
-// rounds 1.02-1.14 up to 0.48, 0.79-0.96 above; three 1.04-1.09 up to 0.65, 0.79-0.97 above; four and more 1.02-1.09
-// up to 0.73, 0.67-0.99 above; 128 filters 1.03-1.10 up to 0.78, 0.81-1.01 above.  Up to 32 and at 96 filters
-// below 0.94 at every share, as the tiles are half empty there.
+// A wave's range is whole units, so the time goes by rounds of 2048 waves; the tiled kernel's goes by rounds of
+// 256 tiles of 128 pixels.  Where its 64- and 128-filter tiles are full the two lie close, and the rounds decide
+// (this kernel's share of its time, 1000 random layers; rounds here : there):
+//   64 filters:   1:1 to 3:3 0.86-0.98, 2:1, 3:2 and 4:3 1.02-1.14;  4:4 0.82-0.87;  5:4 0.94;  7:6 0.87-0.90;
+//                 14:11 0.89;  17:14 0.86
+//   128 filters:  5:2 1.11-1.15;  6:3 0.85-0.95, 7:3 0.96-1.00, 8:3 1.09;  8:4 0.92, 10:4 1.03;  12:5 0.99;
+//                 13:6 0.89-0.95, 15:6 1.01;  18:8 0.89-0.94;  24:10 0.90;  35:15 0.95
+// With fewer filters than its tile has, or 65 to 127, this one is faster at every share (40 to 56 filters
+// 0.65-0.97, up to 32 and 96 below 0.94).
 bool conv_c64_chosen(const ConvGemmArgs& a, int cfg) {
     if (cfg != 60 && (cfg >= 0 || conv_splits_override() > 0)) return false;
     if (a.C != C64 || a.R != 3 || a.S != 3 || a.sh != 1 || a.sw != 1 || a.y_f32 || a.Kf % 8 != 0) return false;
@@ -303,10 +307,9 @@ bool conv_c64_chosen(const ConvGemmArgs& a, int cfg) {
     const int64_t items = units * ((a.Kf + 31) / 32);
     if (a.Kf > 128 || items < (a.Kf == 128 ? 8192 : 1024) || units * (UP * UQ) * 5 > M * 7) return false;
     const int64_t fgroups = (a.Kf + 31) / 32, per = (items < 2048 ? items : 2048) / fgroups;
-    const int64_t rounds = (units + per - 1) / per, slots = rounds * per * (UP * UQ);
-    if (a.Kf == 128) return M * 100 > slots * 78;
-    // more pixels than the rounds but the last could hold, or nearly three quarters of all
-    return a.Kf <= 32 || a.Kf > 64 || M * rounds >= slots * (rounds - 1) || M * 100 >= slots * 74;
+    const int64_t rounds = (units + per - 1) / per, tiled = (M + 32767) / 32768;
+    if (a.Kf == 128) return rounds <= (5 * tiled - 1) / 2;
+    return a.Kf != 64 || rounds <= (4 * tiled - 1) / 3;
 }
 
 hipError_t launch_conv_c64(const ConvGemmArgs& g, hipStream_t stream) {

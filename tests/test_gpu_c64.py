@@ -20,7 +20,8 @@ CASES = [(1, 1, 1, 8, 1), (1, 4, 8, 32, 1), (2, 5, 9, 40, 1), (3, 3, 7, 64, 1), 
          (5, 13, 11, 200, 1)]
 # ... and on either side of the rule that chooses it
 RULE = [(9, 28, 28, 64, 1), (30, 28, 28, 64, 1), (21, 41, 38, 64, 1), (12, 56, 56, 64, 1), (40, 30, 31, 104, 1),
-        (48, 26, 26, 64, 1), (50, 26, 26, 64, 1)]
+        (48, 26, 26, 64, 1), (50, 26, 26, 64, 1), (29, 33, 33, 40, 1), (159, 26, 25, 64, 1), (126, 27, 27, 64, 1),
+        (87, 29, 29, 128, 1), (136, 26, 26, 128, 1)]
 
 
 def _check(tbn, case, knobs, forced):
