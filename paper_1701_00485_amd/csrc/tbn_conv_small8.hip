@@ -313,12 +313,13 @@ int conv_code8_tile(int32_t N, int32_t P, int32_t Q, int32_t K, int64_t n) {
     if (b1 <= 512) return nst >= 12 && b2 <= 256 ? 7 : 5;
     int cfg = K > 128 ? 1 : (K > 64 ? 2 : 3);
     const int bm = 128, bn = cfg == 1 ? 256 : (cfg == 2 ? 128 : 64);
-    // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles beyond 64 filters.  Measured at
-    // 18 k to 48 k rows, reductions of 256 to 10000: 72 to 120 filters 0.88-1.01 (int8) and 0.83-0.93 (fp8)
-    // of the 128-filter tile's time (3 x 3 over 128 channels, 32 k rows, 96 filters 11.5 / 10.3 -> 10.8 /
-    // 9.1 us); 16 to 64 filters 1.06-1.30 and 1.01-1.28 of the 64-filter tile's (64 filters 9.0 / 8.1 there,
-    // 10.6 / 8.8 with 64 x 128, half of whose waves work on filters that do not exist)
-    if (((M + bm - 1) / bm) * ((K + bn - 1) / bn) < 384 && K > 64) cfg = 4;
+    // too few tiles for one wave of blocks: 64-pixel x 128-filter tiles.  Measured against the tile above, over
+    // reductions of 64 to 10000: 72 to 120 filters, 18 k to 48 k rows 0.88-1.01 (int8) and 0.83-0.93 (fp8) of its
+    // time (3 x 3 over 128 channels, 32 k rows, 96 filters 11.5 / 10.3 -> 10.8 / 9.1 us).  Up to 64 filters half of
+    // the waves work on filters that do not exist, which is faster only while a CU has one block: 33 to 64 filters
+    // 0.86-0.97 and 0.86-0.96 at 9 k to 15 k rows (3 x 3 over 256 channels, 64 filters 13.0 / 11.0 -> 12.3 / 10.2),
+    // 0.97-1.24 and 0.96-1.10 at 17 k to 25 k (13.0 / 11.0 -> 15.9 / 12.0); 16 to 64 1.06-1.30 and 1.01-1.28 beyond
+    if (((M + bm - 1) / bm) * ((K + bn - 1) / bn) < 384 && (K > 64 || M <= 256 * 64)) cfg = 4;
     return cfg;
 }
 

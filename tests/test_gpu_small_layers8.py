@@ -21,9 +21,11 @@ CASES = [(1, 1, 1, 16, 1, 1, 1, 1, 0), (1, 1, 31, 16, 32, 1, 1, 1, 0), (1, 1, 33
          (2, 5, 7, 48, 66, 3, 3, 1, 1), (1, 7, 7, 128, 100, 3, 3, 2, 1), (3, 4, 4, 80, 31, 5, 5, 1, 2),
          (2, 6, 5, 192, 65, 3, 1, 1, 2), (1, 9, 9, 16, 96, 7, 7, 1, 3), (1, 3, 3, 1024, 40, 3, 3, 1, 1)]
 
-# ... and where the built-in choice changes beyond them: 64 and 65 filters with fewer than 384 tiles, and with more
+# ... and where the built-in choice changes beyond them: 64 and 65 filters with fewer than 384 tiles, and with more;
+# 33 and 64 filters with 256 tiles of 64 rows and with 257
 RULE = [(1, 131, 129, 16, 64, 1, 1, 1, 0), (1, 131, 129, 16, 65, 1, 1, 1, 0), (1, 131, 129, 16, 31, 3, 3, 1, 1),
-        (1, 222, 223, 16, 64, 1, 1, 1, 0), (1, 222, 223, 16, 65, 1, 1, 1, 0)]
+        (1, 222, 223, 16, 64, 1, 1, 1, 0), (1, 222, 223, 16, 65, 1, 1, 1, 0), (1, 128, 128, 16, 64, 3, 3, 1, 1), (1, 113, 145, 16, 64, 3, 3, 1, 1),
+        (1, 128, 128, 16, 33, 1, 1, 1, 0), (1, 113, 145, 32, 33, 1, 1, 1, 0)]
 
 
 @pytest.mark.parametrize("tile", [-1, 5, 6, 7])
